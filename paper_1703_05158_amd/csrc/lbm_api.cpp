@@ -33,6 +33,8 @@ struct lbm_ctx {
     void *pop[2] = {nullptr, nullptr};
     int cur = 0;                       // pop[cur] holds the current (post-collision) state
     uint16_t *own = nullptr;
+    uint32_t *bits = nullptr;          // solid bitmap of own (bit_row_words)
+    void *lrec = nullptr;              // (max_walls + max_bodies) * kLinkRecBytes: link records by owner code
     uint8_t *wall_map = nullptr;
     double *tab[2] = {nullptr, nullptr};
     int ts = 0;                        // tab[ts]: bodies of the current state's geometry
@@ -152,6 +154,8 @@ GeomArgs geom(const lbm_ctx *h)
     g.bodies = h->tab[h->ts];
     g.nb = h->nb_state;
     g.own = h->own;
+    g.bits = h->bits;
+    g.lrec = h->lrec;
     g.pop = h->pop[h->cur];
     g.rho0 = (float)h->cfg.rho0;
     return g;
@@ -255,10 +259,12 @@ FusedArgs fused_args(const lbm_ctx *h)
     f.n_walls = h->n_walls;
     f.nb = h->nb_state;
     f.halfway = h->cfg.bb_mode == LBM_BB_HALFWAY;
-    f.bodies = h->tab[h->ts];
-    f.wrec = h->wrec;
     f.fsum = h->fsum[h->fcur];
     f.wall_base = h->cfg.max_bodies;
+    f.lrec = h->lrec;
+    f.bits = h->bits;
+    f.inv_ntx = quick_inv(f.s.ntx);
+    f.inv_nty = quick_inv(f.s.nty);
     return f;
 }
 
@@ -337,11 +343,13 @@ lbm_status upload_wall_records(lbm_ctx *h, const double *wt, int n)
 lbm_status rasterize_full(lbm_ctx *h)
 {
     GeomArgs g = geom(h);
+    HIP_TRY(h, launch_link_records(g, h->wrec, h->stream));
     g.bodies2 = g.bodies;  // stamp only
     g.nb2 = g.nb;
     g.nb = 0;
     HIP_TRY(h, launch_walls_init(h->wall_map, h->own, h->N, h->stream));
     HIP_TRY(h, launch_geometry(h->cfg.storage, g, h->stream));
+    HIP_TRY(h, launch_solid_bits(g, h->stream));
     return LBM_OK;
 }
 
@@ -572,6 +580,9 @@ lbm_status lbm_create(const lbm_config *cfg, lbm_handle *out)
     set_tile_shape(h, (c.nx % 64 != 0 && (c.nx % 32 == 0 || c.nx < 32)) ? kTile32x4x2 : kTile64x2x2);
     if (dalloc(h, &h->pop[0], popb) != hipSuccess || dalloc(h, &h->pop[1], popb) != hipSuccess ||
         dalloc(h, &h->own, sizeof(uint16_t) * N + 4) != hipSuccess ||
+        dalloc(h, &h->bits, sizeof(uint32_t) * (bit_row_words(c.nx) * ((size_t)c.ny * (size_t)c.nz) + kBitPad)) !=
+            hipSuccess ||
+        dalloc(h, &h->lrec, (size_t)kLinkRecBytes * std::max(nbt, 1)) != hipSuccess ||
         dalloc(h, &h->wall_map, (size_t)N) != hipSuccess ||
         dalloc(h, &h->tab[0], sizeof(double) * kBodyStride * std::max(c.max_bodies, 1)) != hipSuccess ||
         dalloc(h, &h->tab[1], sizeof(double) * kBodyStride * std::max(c.max_bodies, 1)) != hipSuccess ||
@@ -615,7 +626,7 @@ void lbm_destroy(lbm_handle h)
     (void)hipStreamSynchronize(h->stream);
     for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
     free_wall_links(h);
-    void *dev[] = {h->pop[0], h->pop[1], h->own, h->wall_map, h->tab[0], h->tab[1], h->walls, h->wrec,
+    void *dev[] = {h->pop[0], h->pop[1], h->own, h->bits, h->lrec, h->wall_map, h->tab[0], h->tab[1], h->walls, h->wrec,
                    h->acc, h->fsum[0], h->fsum[1], h->order, h->flag, h->scratch, h->zstate, h->zpart};
     for (void *p : dev)
         if (p) (void)hipFree(p);
@@ -1138,6 +1149,8 @@ lbm_status lbm_set_state(lbm_handle h, const void *buf, size_t bytes)
     h->nb_next = hd.nb_next;
     h->dirty = hd.dirty != 0;
     h->steps_done = hd.steps_done;
+    HIP_TRY(h, launch_solid_bits(geom(h), h->stream));
+    HIP_TRY(h, launch_link_records(geom(h), h->wrec, h->stream));
     h->initialized = true;
     h->geom_gen++;
     TRY(reset_sums(h));
@@ -1596,6 +1609,8 @@ lbm_status batch_build(lbm_batch_ctx *b)
         st.nty = (h->cfg.ny + TY - 1) / TY;
         st.ntz = (h->cfg.nz + TZ - 1) / TZ;
         st.n_tiles = st.ntx * st.nty * st.ntz;
+        bm.f.inv_ntx = quick_inv(st.ntx);
+        bm.f.inv_nty = quick_inv(st.nty);
         bm.fin = FinishArgs{h->fsum[h->fcur], h->cfg.max_bodies, h->nb_state, h->n_walls, h->acc, nullptr};
         bm.pop[0] = h->pop[0];
         bm.pop[1] = h->pop[1];

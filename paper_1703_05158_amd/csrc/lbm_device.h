@@ -15,18 +15,34 @@ constexpr int CX[kQ] = {0, -1, 0, 0, -1, -1, -1, -1, 0, 0, 1, 0, 0, 1, 1, 1, 1, 
 constexpr int CY[kQ] = {0, 0, -1, 0, -1, 1, 0, 0, -1, -1, 0, 1, 0, 1, -1, 0, 0, 1, 1};
 constexpr int CZ[kQ] = {0, 0, 0, -1, 0, 0, -1, 1, -1, 1, 0, 0, 1, 0, 0, 1, -1, 1, -1};
 
-constexpr uint64_t pack_dir(const int (&c)[kQ])
+// The directions whose component is `sign`, as a bit per direction.
+constexpr uint32_t dir_bits(const int (&c)[kQ], int sign)
 {
-    uint64_t v = 0;
-    for (int i = 0; i < kQ; ++i) v |= (uint64_t)(c[i] + 1) << (2 * i);
+    uint32_t v = 0;
+    for (int i = 0; i < kQ; ++i) v |= (uint32_t)(c[i] == sign) << i;
     return v;
 }
-constexpr uint64_t kPX = pack_dir(CX), kPY = pack_dir(CY), kPZ = pack_dir(CZ);
 
-// Runtime-indexed lookups (cold paths) without memory traffic.
-__device__ __forceinline__ int dcx(int i) { return (int)((kPX >> (2 * i)) & 3) - 1; }
-__device__ __forceinline__ int dcy(int i) { return (int)((kPY >> (2 * i)) & 3) - 1; }
-__device__ __forceinline__ int dcz(int i) { return (int)((kPZ >> (2 * i)) & 3) - 1; }
+// Runtime-indexed lookups without memory traffic: all ones where the
+// component of direction i is +1 (pos) or -1 (neg), else 0; each is one
+// bit-field instruction.
+struct Comp {
+    int pos, neg;
+    __device__ __forceinline__ int value() const { return neg - pos; }
+    // the component times n, without a multiplication
+    __device__ __forceinline__ int times(int n) const { return (n & pos) - (n & neg); }
+};
+template <uint32_t kPos, uint32_t kNeg>
+__device__ __forceinline__ Comp comp_of(int i)
+{
+    return Comp{(int)__builtin_amdgcn_sbfe(kPos, i, 1), (int)__builtin_amdgcn_sbfe(kNeg, i, 1)};
+}
+__device__ __forceinline__ Comp comp_x(int i) { return comp_of<dir_bits(CX, 1), dir_bits(CX, -1)>(i); }
+__device__ __forceinline__ Comp comp_y(int i) { return comp_of<dir_bits(CY, 1), dir_bits(CY, -1)>(i); }
+__device__ __forceinline__ Comp comp_z(int i) { return comp_of<dir_bits(CZ, 1), dir_bits(CZ, -1)>(i); }
+__device__ __forceinline__ int dcx(int i) { return comp_x(i).value(); }
+__device__ __forceinline__ int dcy(int i) { return comp_y(i).value(); }
+__device__ __forceinline__ int dcz(int i) { return comp_z(i).value(); }
 __host__ __device__ constexpr int opp(int i) { return i == 0 ? 0 : (i <= 9 ? i + 9 : i - 9); }
 
 // Weights: w0 = 1/3, axis directions (1,2,3,10,11,12) 1/18, others 1/36.

@@ -2,13 +2,14 @@
 // and store of a 256-node tile in one pass over HBM.
 //
 // Per tile (one workgroup, one node per thread):
-//  1. Each thread loads the owner codes of its node and of its 18 pull
-//     sources, and issues the pulls of its node whose source is fluid (the
-//     streaming equation of Sec. 2.2) straight into the tile's LDS array of
+//  1. Each wavefront reads which of its nodes and of their pull sources are
+//     solid from the solid bitmap, as lane masks in scalar registers, and
+//     issues the pulls of fluid nodes from fluid sources (the streaming
+//     equation of Sec. 2.2) straight into the tile's LDS array of
 //     populations.
-//  2. Each fluid node marks the directions whose pull source is a solid node
-//     (a cut link, Sec. 2.3); the links of the tile are listed in LDS and
-//     spread over the workgroup's threads.  Per link: the value of the
+//  2. A direction whose pull source is a solid node is a cut link (Sec. 2.3);
+//     the links of the tile are listed in LDS and spread over the
+//     workgroup's threads.  Per link: the value of the
 //     population the node receives (the q < 1/2 and q >= 1/2 branches with
 //     the moving-boundary term of eq. moving_boundary_velocity, walls at
 //     q = 1/2), formed from the current state at the node and at the node
@@ -24,6 +25,17 @@
 //     forces of the step.  Integer sums do not depend on the order of the
 //     additions, so the forces are the same bit for bit for every launch,
 //     tile shape and batch.
+// What bounds it: with FP32 storage HBM and issue about equally, with 16-bit
+// storage instruction issue.  A wavefront issues vector and scalar
+// instructions on separate ports at the same rate (one per SIMD in four
+// cycles), so both counts matter.  On the 128x128x512 duct with 4000 spheres,
+// tile 64x2x2, per wavefront: 692 vector and 599 scalar instructions (FP16),
+// 219 us per launch; with owner codes loaded per pull source and a scan over
+// the workgroup (897 vector, 410 scalar, 18 loads more) it took 244 us, FP32
+// 261 against 287 us.  Masks kept per direction for the pulls as well (1305
+// scalar instructions) took 316 us: the pulls therefore go to every fluid
+// lane, and the few values pulled from solid sources are replaced later.
+//
 // The link arithmetic is that of the boundary-link pass (lbm_linkmath.h), so
 // the populations equal, bit for bit, those of the link pass followed by the
 // pull-collide kernel.
@@ -63,6 +75,20 @@ struct FusedLds {
 };
 static_assert(sizeof(FusedLds) <= 23040, "seven workgroups per CU");
 
+// The step's arguments where they lie in memory (the kernel's argument
+// segment, or a batch member's record), read by scalar loads: nothing writes
+// them while a kernel runs.
+typedef const __attribute__((address_space(4))) FusedArgs *ArgPtr;
+
+// The same pointer, unknown to the compiler: what is read through it is
+// loaded again.  A tile works in phases that need different arguments, and
+// all of them together with the lane masks do not fit in scalar registers.
+__device__ __forceinline__ ArgPtr reread(ArgPtr p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 // v 2^32 rounded to the nearest integer, ties to even, as a two's-complement
 // 64-bit value.  While |v 2^32| < 2^51 one FP64 add of 1.5 2^52 leaves that
 // integer in the low mantissa bits (to_fix_fast, for |v| < kFixFastLimit);
@@ -82,17 +108,17 @@ __device__ __forceinline__ unsigned long long to_fix_slow(double v)
 }
 
 // Global fixed-point sums of owner code `key` (tile t picks the wall copy).
-__device__ __forceinline__ unsigned long long *fix_slot(const FusedArgs &f, int key, int t)
+__device__ __forceinline__ unsigned long long *fix_slot(ArgPtr f, int key, int t)
 {
-    const int e = key < f.n_walls ? f.wall_base + key * kWallRep + (t & (kWallRep - 1)) : key - f.n_walls;
-    return f.fsum + 6 * (size_t)e;
+    const int e = key < f->n_walls ? f->wall_base + key * kWallRep + (t & (kWallRep - 1)) : key - f->n_walls;
+    return f->fsum + 6 * (size_t)e;
 }
 
 // Add one link's fixed-point force and torque to the tile's slot of body
 // `key` (the lane's copy of the sums), or straight to the global sums when
 // the table is full.  A slot is claimed once by compare-and-swap; later
 // lookups read it.
-__device__ __forceinline__ void table_add(const FusedArgs &f, FusedLds &lds, int key, const unsigned long long (&v)[6],
+__device__ __forceinline__ void table_add(ArgPtr f, FusedLds &lds, int key, const unsigned long long (&v)[6],
                                           int t)
 {
     int s = key & (kRec - 1);
@@ -124,120 +150,175 @@ __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70)
 // clobbers memory, so the compiler moves no memory access across it.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Exclusive prefix of cnt (0 <= cnt < 64) over the workgroup, its total, and
-// whether any lane has flag set; through LDS (wtot: one word per wavefront)
-// with an LDS-only barrier.
-__device__ __forceinline__ int tile_scan(int cnt, bool flag, int *wtot, int &tot, bool &any)
+// Quotient and remainder of t / d for a uniform t >= 0, with inv =
+// quick_inv(d).
+__device__ __forceinline__ int quick_div(int t, int d, uint32_t inv, int &rem)
 {
-    constexpr int kWaves = kBlock / 64;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    int pos = 0, wsum = 0;
-#pragma unroll
-    for (int b = 0; b < 6; ++b) {
-        const unsigned long long mb = __ballot((cnt >> b) & 1);
-        pos += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mb >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mb, 0u)) << b;
-        wsum += __popcll(mb) << b;
+    int q = (int)__umulhi((uint32_t)t, inv);
+    rem = t - q * d;
+    if (rem >= d) {
+        ++q;
+        rem -= d;
     }
-    const bool wflag = __ballot(flag) != 0;  // on every lane (a ballot sees the active lanes only)
-    if (lane == 0) wtot[wv] = wsum | (wflag ? 1 << 20 : 0);  // wsum < 2^13
-    lds_barrier();
-    tot = 0;
-    int fl = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        const int t = wtot[w];
-        if (w < wv) pos += t & 0xFFFFF;
-        tot += t & 0xFFFFF;
-        fl |= t;
-    }
-    any = (fl >> 20) & 1;
-    return pos;
+    return q;
 }
 
-// Index offsets of a node's periodic neighbours along each axis: m = to the
-// node at coordinate - 1, p = to the node at + 1.
-struct NbOff {
-    int xm, xp, ym, yp, zm, zp;
+// A wavefront's share of a tile, 64 / TX rows of TX nodes at z from row y on,
+// as 64-bit lane masks in scalar registers: the lanes inside the lattice,
+// those of fluid nodes, and per direction the fluid lanes whose pull source
+// x - c_i is solid (a cut link).  Everything here is scalar: the windows of
+// the solid bitmap are scalar loads, a direction's mask is a shift of one of
+// them, and using a mask as the lanes of a load or store costs no vector
+// instruction.
+template <int TX>
+struct WaveMasks {
+    static constexpr int kRows = 64 / TX;
+    uint64_t in, fluid, cut[kQ];
 };
 
-__device__ __forceinline__ NbOff nb_off(int x, int y, int z, int nx, int ny, int nz)
+// The rows of a wavefront (z, y .. y + R - 1) and their periodic neighbours, as
+// scalars: y - 1 .. y + R and z - 1 .. z + 1.  A wavefront outside the lattice
+// takes rows inside it.
+template <int R>
+struct WaveRows {
+    int y[R + 2], z[3];
+    __device__ __forceinline__ WaveRows(int wy, int wz, int ny, int nz)
+    {
+        y[1] = min(wy, ny - 1);
+        y[0] = y[1] == 0 ? ny - 1 : y[1] - 1;
+#pragma unroll
+        for (int k = 2; k < R + 2; ++k) y[k] = y[k - 1] + 1 >= ny ? 0 : y[k - 1] + 1;
+        z[1] = min(wz, nz - 1);
+        z[0] = z[1] == 0 ? nz - 1 : z[1] - 1;
+        z[2] = z[1] + 1 >= nz ? 0 : z[1] + 1;
+    }
+};
+
+template <int TX>
+__device__ __forceinline__ void wave_masks(ArgPtr f, int x0, int y, int z, const WaveRows<64 / TX> &w,
+                                           WaveMasks<TX> &m)
 {
-    const int nxy = nx * ny;
-    NbOff o;
-    o.xm = x == 0 ? nx - 1 : -1;
-    o.xp = x + 1 >= nx ? 1 - nx : 1;
-    o.ym = y == 0 ? nxy - nx : -nx;
-    o.yp = y + 1 >= ny ? nx - nxy : nx;
-    o.zm = z == 0 ? nxy * (nz - 1) : -nxy;
-    o.zp = z + 1 >= nz ? nxy * (1 - nz) : nxy;
-    return o;
+    constexpr int R = 64 / TX;
+    constexpr uint64_t kOnes = TX == 64 ? ~0ull : (1ull << (TX & 63)) - 1;
+    typedef const __attribute__((address_space(4))) char *ScalarPtr;  // scalar loads: nothing writes it meanwhile
+    typedef const __attribute__((address_space(4))) uint32_t *ScalarWords;
+    const int nx = f->s.nx, ny = f->s.ny, nz = f->s.nz;
+    m.in = 0;
+    const uint64_t row_in = x0 + TX <= nx ? kOnes : (1ull << (nx - x0)) - 1;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (z < nz && y + r < ny) m.in |= row_in << (r * TX & 63);
+    m.fluid = 0;
+#pragma unroll
+    for (int i = 1; i < kQ; ++i) m.cut[i] = 0;
+    if (!m.in) return;
+    const uint32_t rw = 4u * (uint32_t)bit_row_words(nx);
+    const ScalarPtr bits = (ScalarPtr)(uintptr_t)f->bits;
+    uint32_t yw[R + 2];  // byte offsets of the rows' windows within a plane
+#pragma unroll
+    for (int k = 0; k < R + 2; ++k) yw[k] = rw * (uint32_t)w.y[k] + (uint32_t)(x0 >> 5) * 4u;
+    // solid bits of TX nodes of the rows y - 1 .. y + R and z - 1 .. z + 1:
+    // of the nodes x - 1 (s = 0), x (1) and x + 1 (2)
+    uint64_t lo[3][R + 2];
+    uint32_t hi[3][R + 2];
+#pragma unroll
+    for (int dz = 0; dz < 3; ++dz) {
+        const uint32_t zw = rw * (uint32_t)ny * (uint32_t)w.z[dz];
+#pragma unroll
+        for (int k = 0; k < R + 2; ++k) {
+            const ScalarWords p = (ScalarWords)(bits + (uint64_t)(yw[k] + zw));
+            lo[dz][k] = (uint64_t)p[0] | (uint64_t)p[1] << 32;
+            hi[dz][k] = TX == 64 ? p[2] : 0u;
+        }
+    }
+    const int half = TX == 16 ? (x0 & 16) : 0;
+    auto window = [&](int dz, int k, int s) -> uint64_t {
+        if (TX == 64) return s == 0 ? lo[dz][k] : lo[dz][k] >> s | (uint64_t)hi[dz][k] << ((64 - s) & 63);
+        return (lo[dz][k] >> (half + s)) & kOnes;
+    };
+    auto rows = [&](int cx, int cy, int cz) {  // solid bits of the sources x - c of the wavefront's nodes
+        uint64_t v = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) v |= window(1 - cz, r + 1 - cy, 1 - cx) << (r * TX & 63);
+        return v;
+    };
+    m.fluid = m.in & ~rows(0, 0, 0);
+    // nothing solid near the wavefront: no link
+    uint64_t any = 0;
+    uint32_t any_hi = 0;
+#pragma unroll
+    for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+        for (int k = 0; k < R + 2; ++k) {
+            any |= lo[dz][k];
+            any_hi |= hi[dz][k];
+        }
+    if (!(any | any_hi)) return;
+#pragma unroll
+    for (int i = 1; i < kQ; ++i) m.cut[i] = m.fluid & rows(CX[i], CY[i], CZ[i]);
 }
 
-// Index of x - c_i, the source of the pull of population i (i compile-time).
-__device__ __forceinline__ uint32_t pull_src(uint32_t idx, const NbOff &o, int i)
-{
-    int d = 0;
-    if (CX[i] > 0) d += o.xm;
-    if (CX[i] < 0) d += o.xp;
-    if (CY[i] > 0) d += o.ym;
-    if (CY[i] < 0) d += o.yp;
-    if (CZ[i] > 0) d += o.zm;
-    if (CZ[i] < 0) d += o.zp;
-    return (uint32_t)((int)idx + d);
-}
-
-// Link j of the tile's list: its value into LDS, its momentum into the force
-// table.  Walls are records like spheres: reference point, velocity, no
+// Item `it` of the tile's list: returns the link's value as the stored bits,
+// its momentum goes into the force table.  Walls are records like spheres: reference point, velocity, no
 // spin, q = 1/2 and no minimum image (their arm is about the reference
 // point).
 template <int S, int TX, int TY, int TZ>
-__device__ __forceinline__ void fused_link(const FusedArgs &f, FusedLds &lds, int x0, int y0, int z0, int j, int t)
+__device__ __forceinline__ uint32_t fused_link(ArgPtr f, const typename Store<S>::T *__restrict__ src, FusedLds &lds,
+                                               int x0, int y0, int z0, uint32_t it, int t)
 {
     using St = Store<S>;
     using T = typename St::T;
-    const StepArgs &a = f.s;
-    const T *__restrict__ src = static_cast<const T *>(a.src);
-    const size_t Ns = (size_t)a.Ns;
-    const int nx = a.nx, ny = a.ny, nz = a.nz;
-    const uint32_t it = lds.item[j];
-    const int nl = (int)(it >> 24), I = (int)((it >> 19) & 31u), K = opp(I);
+    const size_t Ns = (size_t)f->s.Ns;
+    const int nx = f->s.nx, ny = f->s.ny, nz = f->s.nz;
+    const int nl = (int)(it >> 24), I = (int)((it >> 19) & 31u), K = I <= 9 ? I + 9 : I - 9;
     const bool behind = (it >> 18) & 1u;
-    const int x = x0 + nl % TX, y = y0 + (nl / TX) % TY, z = z0 + nl / (TX * TY);
-    const uint32_t xi = (uint32_t)(x + nx * (y + ny * z));
-    // owner code of the solid node p = x - c_I (periodic; a cache hit: the
-    // node's own lane loaded it when it listed the link)
-    const int os = *at(a.own, (uint32_t)(wrap_add(x, -dcx(I), nx) +
-                                         nx * (wrap_add(y, -dcy(I), ny) + ny * wrap_add(z, -dcz(I), nz))));
-    const bool sphere = os >= f.n_walls;
-    const bool exact_q = sphere && !f.halfway;
+    const int lx = nl % TX, ly = (nl / TX) % TY, lz = nl / (TX * TY);
+    const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
+    const Comp cx = comp_x(I), cy = comp_y(I), cz = comp_z(I);
+    const int nxy = nx * ny;
+    // the node's index, without multiplications per lane
+    uint32_t xi = (uint32_t)(x0 + nx * y0 + nxy * z0 + lx);
+#pragma unroll
+    for (int b = 1; b < TY; b <<= 1) xi += ly & b ? (uint32_t)(b * nx) : 0u;
+#pragma unroll
+    for (int b = 1; b < TZ; b <<= 1) xi += lz & b ? (uint32_t)(b * nxy) : 0u;
+    // the solid node p = x - c_I and the node behind x, x + c_I: one step of
+    // the index, or, in a wavefront with a node on the box's faces, with the
+    // periodic wrap
+    const uint32_t step = (uint32_t)(cx.value() + cy.times(nx) + cz.times(nxy));
+    uint32_t pi = xi - step, bi = xi + step;
+    if (__ballot((unsigned)(x - 1) >= (unsigned)(nx - 2) || (unsigned)(y - 1) >= (unsigned)(ny - 2) ||
+                 (unsigned)(z - 1) >= (unsigned)(nz - 2))) {
+        const int ax = cx.value(), ay = cy.value(), az = cz.value();
+        pi = (uint32_t)(wrap_add(x, -ax, nx) + nx * (wrap_add(y, -ay, ny) + ny * wrap_add(z, -az, nz)));
+        bi = (uint32_t)(wrap_add(x, ax, nx) + nx * (wrap_add(y, ay, ny) + ny * wrap_add(z, az, nz)));
+    }
+    // population d of node n, as stored
+    auto stored = [&](int d, uint32_t n) { return src[(uint64_t)(uint32_t)d * (uint32_t)Ns + n]; };
+    const int os = *at(f->s.own, pi);
+    const bool sphere = os >= f->n_walls;
+    const bool exact_q = sphere && !f->halfway;
     // the solid's record and the populations, in one round trip: the record
     // first, and the populations as stored values, converted only once all
     // are in flight (a conversion inside a branch would wait for its load,
     // and for everything issued before it)
-    const double *B = sphere ? f.bodies + (size_t)(os - f.n_walls) * kBodyStride : f.wrec + (size_t)os * kBodyStride;
-    const SphereK sk = sphere_k(B);
-    const T rk = *at(src + (size_t)K * Ns, xi);
+    const SphereK sk = at(static_cast<const LinkRec *>(f->lrec), (uint32_t)os)->k;
+    const T rk = stored(K, xi);
     T ra = T(0), rb = T(0);
     if (exact_q) {
-        ra = *at(src + (size_t)I * Ns, xi);
-        if (behind) {
-            // the node behind x, x + c_I (periodic)
-            const uint32_t xb = (uint32_t)(wrap_add(x, dcx(I), nx) + nx * (wrap_add(y, dcy(I), ny) + ny * wrap_add(z, dcz(I), nz)));
-            rb = *at(src + (size_t)K * Ns, xb);
-        }
+        ra = stored(I, xi);
+        if (behind) rb = stored(K, bi);
     }
     const float fk = St::cvt(rk), fa = St::cvt(ra), fb = St::cvt(rb);
-    const LinkGeo g = link_geo(sk, exact_q, sphere, a.rho0, x, y, z, nx, ny, nz, I);
+    const LinkGeo g = link_geo(sk, exact_q, sphere, f->s.rho0, x, y, z, nx, ny, nz, I);
     const float vr = St::round(link_value(g.q, fk, fa, fb, behind, g.mw));
-    lds.val[I][nl] = St::to_bits(vr);  // a slot no pull is loaded into
     double acc[6];
-    const double mom = link_momentum(fk, vr, I, a.rho0);
+    const double mom = link_momentum(fk, vr, I, f->s.rho0);
     link_force_terms(mom, I, g, acc);
     unsigned long long v[6];
     // F = -mom c_I: its fixed-point components are -c M with M = fix(mom)
     // (the rounding is odd-symmetric).  One range test for the four
     // conversions (to_fix's two ways, taken together).
-    const int cI[3] = {dcx(I), dcy(I), dcz(I)};
     unsigned long long M;
     const double big =
         fmax(fmax(__builtin_fabs(mom), __builtin_fabs(acc[3])), fmax(__builtin_fabs(acc[4]), __builtin_fabs(acc[5])));
@@ -250,130 +331,173 @@ __device__ __forceinline__ void fused_link(const FusedArgs &f, FusedLds &lds, in
 #pragma unroll
         for (int c = 3; c < 6; ++c) v[c] = to_fix_slow(acc[c]);
     }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) v[c] = cI[c] > 0 ? 0ull - M : (cI[c] < 0 ? M : 0ull);
+    // -c M from the component's masks: M ^ s - s is -M where s is all ones
+    auto signed_part = [&](const Comp &c) {
+        const unsigned long long s = (unsigned long long)(long long)c.pos;
+        return ((M ^ s) - s) & (unsigned long long)(long long)(c.pos | c.neg);
+    };
+    v[0] = signed_part(cx);
+    v[1] = signed_part(cy);
+    v[2] = signed_part(cz);
     table_add(f, lds, os, v, t);
+    return St::to_bits(vr);
+}
+
+// Issue the pulls of directions I .. 18 of the active lanes into the row
+// of lds.val that starts at node `first` (the wavefront's): xb, yb, zb are the
+// byte offsets of the source by the component of -c_i (-1, 0, 1).
+template <int S, int I>
+__device__ __forceinline__ void pull_from(const char *src, size_t Ns, const uint32_t (&xb)[3], const uint32_t (&yb)[3],
+                                          const uint32_t (&zb)[3], FusedLds &lds, int first)
+{
+    if constexpr (I < kQ) {
+        using T = typename Store<S>::T;
+        constexpr int kBytes = S == 0 ? 4 : 2;
+        const uint32_t off = xb[1 - CX[I]] + (yb[1 - CY[I]] + zb[1 - CZ[I]]);
+        const T *p = reinterpret_cast<const T *>(src + (size_t)I * Ns * sizeof(T) + off);
+        __builtin_amdgcn_global_load_lds(p, (__attribute__((address_space(3))) void *)&lds.val[I][first], kBytes, 0, 0);
+        pull_from<S, I + 1>(src, Ns, xb, yb, zb, lds, first);
+    }
 }
 
 // Tile t of the lattice of f.  Every thread of the workgroup calls it (it
 // holds barriers); lds may be reused by the next call.
 template <int S, int TX, int TY, int TZ>
-__device__ __forceinline__ void fused_tile(const FusedArgs &f, int t, FusedLds &lds)
+__device__ __forceinline__ void fused_tile(ArgPtr f, const void *srcv, void *dstv, int t, FusedLds &lds)
 {
     static_assert(TX * TY * TZ == kBlock, "tile must hold one workgroup");
     using St = Store<S>;
     using T = typename St::T;
-    const StepArgs &a = f.s;
-    const T *__restrict__ src = static_cast<const T *>(a.src);
-    T *__restrict__ dst = static_cast<T *>(a.dst);
-    const size_t Ns = (size_t)a.Ns;
-    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const T *__restrict__ src = static_cast<const T *>(srcv);
+    const size_t Ns = (size_t)f->s.Ns;
+    const int nx = f->s.nx, ny = f->s.ny, nz = f->s.nz;
 
-    const int tid = threadIdx.x;
-    const int r = t / a.ntx;
-    const int x0 = (t - r * a.ntx) * TX, y0 = (r % a.nty) * TY, z0 = (r / a.nty) * TZ;
-    const int x = x0 + tid % TX, y = y0 + (tid / TX) % TY, z = z0 + tid / (TX * TY);
-    const bool in = x < nx && y < ny && z < nz;
-    const uint32_t idx = in ? (uint32_t)(x + nx * (y + ny * z)) : 0u;
-    const NbOff no = nb_off(x, y, z, nx, ny, nz);
-    auto src_idx = [&](int i) { return pull_src(idx, no, i); };
+    constexpr int R = 64 / TX;  // rows of a wavefront
+    // (opaque: a kernel that loops over tiles would keep what follows from the
+    // thread index in registers from tile to tile)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int tx, ty;
+    const int r = quick_div(t, f->s.ntx, f->inv_ntx, tx);
+    const int x0 = tx * TX, z0 = quick_div(r, f->s.nty, f->inv_nty, ty) * TZ, y0 = ty * TY;
+    // the wavefront's rows: at z from wy on; the lane's node (x, y, z)
+    const int wy = y0 + wv * R % TY, z = z0 + wv * R / TY;
+    const int lx = lane % TX, x = x0 + lx, y = wy + lane / TX;
 
-    // 1. owner codes of the node and of its 18 pull sources (loaded before
-    //    anything else, so that waiting for them waits for nothing later)
-    const uint16_t o = in ? *at(a.own, idx) : uint16_t(0);
-    uint16_t on[kQ];
-    if (in) {
+    // 1. which lanes are fluid, and which directions of each are cut
+    const WaveRows<R> rows(wy, z, ny, nz);
+    WaveMasks<TX> mk;
+    wave_masks<TX>(f, x0, wy, z, rows, mk);
+    // byte offsets of the lane's pull sources x - c_i within a direction's
+    // array (below 2^32): a lane part for the x neighbour and, where the
+    // wavefront holds several rows, the y neighbour, and a scalar part for
+    // the rest
+    constexpr uint32_t kB = sizeof(T);
+    const uint32_t xb[3] = {kB * (uint32_t)(x == 0 ? nx - 1 : x - 1), kB * (uint32_t)x,
+                            kB * (uint32_t)(x + 1 >= nx ? 0 : x + 1)};
+    uint32_t yb[3], zb[3];  // lane part of y (scalar where R == 1) and scalar part of z
 #pragma unroll
-        for (int i = 1; i < kQ; ++i) on[i] = *at(a.own, src_idx(i));
+    for (int k = 0; k < 3; ++k) {
+        yb[k] = kB * (uint32_t)(nx * (R == 1 ? rows.y[k] : wrap1(y + k - 1, ny)));
+        zb[k] = kB * (uint32_t)(nx * ny) * (uint32_t)rows.z[k];
     }
-    const bool fluid = in && o >= kVacated;
+
     lds_barrier();  // the previous tile's readers of lds are done
-    // The owner codes are waited for before anything else is loaded: the
-    // compiler does not count loads into LDS, so a later wait for an owner
-    // code would wait for all of them.
-    wait_vmem();
-    uint32_t solid = 0;  // pull sources owned by a solid
-    if (fluid) {
+    // the pulls of the fluid nodes go straight from HBM into lds.val (one
+    // word per lane, 16-bit values zero-extended), in flight while the tile's
+    // links are listed and formed.  A pull from a solid source brings a value
+    // that nobody reads: the link's value replaces it once it has landed.
+    if (__builtin_amdgcn_inverse_ballot_w64(mk.fluid))
+        pull_from<S, 0>(reinterpret_cast<const char *>(src), Ns, xb, yb, zb, lds, wv * 64);
+    // listed links: not the inflow plane's directions from the removed domain
+    const bool inflow = z == f->s.zieb_z;
+    auto links_of = [&](const WaveMasks<TX> &m, int i) -> uint64_t { return inflow && CZ[i] == 1 ? 0ull : m.cut[i]; };
+    int cnt = 0;
 #pragma unroll
-        for (int i = 1; i < kQ; ++i)
-            if (on[i] < kVacated) solid |= 1u << i;
-        // the node's pulls from fluid sources go straight from HBM into
-        // lds.val (one word per lane, 16-bit values zero-extended), in
-        // flight while the tile's links are listed and formed; the slot of
-        // a cut link is left to the link's value
-        constexpr int kBytes = S == 0 ? 4 : 2;  // an int: the builtin takes a 32-bit size
-        const int wbase = __builtin_amdgcn_readfirstlane(tid & ~63);  // the wavefront's LDS row offset
-#pragma unroll
-        for (int i = 0; i < kQ; ++i)
-            if (!((solid >> i) & 1u))
-                __builtin_amdgcn_global_load_lds(at(src + (size_t)i * Ns, i ? src_idx(i) : idx),
-                                                 (__attribute__((address_space(3))) void *)&lds.val[i][wbase],
-                                                 kBytes, 0, 0);
-    }
-    // cut links: not the inflow plane's directions from the removed domain
-    uint32_t m = solid;
-    if (z == a.zieb_z) {
-#pragma unroll
-        for (int i = 1; i < kQ; ++i)
-            if (CZ[i] == 1) m &= ~(1u << i);
-    }
+    for (int i = 1; i < kQ; ++i) cnt += __popcll(links_of(mk, i));
     for (int k = tid; k < kRec; k += kBlock) lds.key[k] = -1;
     for (int k = tid; k < kCopies * kRec * 6; k += kBlock) (&lds.sum[0][0][0])[k] = 0ull;
-    int tot;
-    bool any_fluid;
-    const int pos = tile_scan(__popc(m), fluid, lds.wtot, tot, any_fluid);  // its barrier also publishes the table's reset
-    if (!any_fluid) return;
+    if (lane == 0) lds.wtot[wv] = cnt | (mk.fluid ? 1 << 20 : 0);  // cnt <= 64 * 18
+    lds_barrier();  // publishes the counts and the table's reset
+    int tot = 0, first = 0, flags = 0;  // the tile's links, those of the wavefronts before, whether any node is fluid
+#pragma unroll
+    for (int w = 0; w < kBlock / 64; ++w) {
+        const int v = __builtin_amdgcn_readfirstlane(lds.wtot[w]);
+        if (w < wv) first += v & 0xFFFFF;
+        tot += v & 0xFFFFF;
+        flags |= v;
+    }
+    if (!(flags >> 20)) return;
 
     // 2. the tile's links, listed and spread over the workgroup, in rounds
     //    of kLinkCap.  An item is node << 24 | I << 19 | (the node behind x
-    //    is fluid) << 18; each lane walks only its own cut directions (a
-    //    wavefront's walk is as long as its lanes' largest count, not 18).
-    //    A link's value goes into its node's slot of lds.val, which no pull
-    //    is loaded into, so the pulls stay in flight.
-    // bit i: the pull source of opp(i), x + c_i, is fluid (opp pairs i, i + 9)
-    const uint32_t nsolid = ~solid;
-    const uint32_t behind_bits = ((nsolid >> 9) & 0x3FEu) | ((nsolid << 9) & 0x7FC00u);
-    auto list = [&](int base) {  // the items with list index in [base, base + kLinkCap)
-        uint32_t mm = m;
-        int k = pos - base;
-        while (mm) {
-            const int i = __builtin_ctz(mm);
-            mm &= mm - 1u;
-            if (k >= 0 && k < kLinkCap)
-                lds.item[k] = ((uint32_t)tid << 24) | ((uint32_t)i << 19) | (((behind_bits >> i) & 1u) << 18);
-            ++k;
+    //    is fluid) << 18.  A wavefront lists its links direction by
+    //    direction, so that neighbouring items read neighbouring nodes of
+    //    the same arrays.  The value of a thread's first link waits until
+    //    every pull of the tile has landed, then replaces what was pulled.
+    auto list = [&](const WaveMasks<TX> &m, int base, bool all) {  // all: or those in [base, base + kLinkCap)
+        int k0 = -base;
+#pragma unroll
+        for (int i = 1; i < kQ; ++i) {
+            const uint64_t c = links_of(m, i);
+            if (__builtin_amdgcn_inverse_ballot_w64(c)) {
+                const int k = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(c >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)c, first + k0));
+                // the source of opp(i) is the node behind x, x + c_i
+                const uint32_t behind = __builtin_amdgcn_inverse_ballot_w64(m.cut[opp(i)]) ? 0u : 1u << 18;
+                if (all || (k >= 0 && k < kLinkCap)) lds.item[k] = (uint32_t)tid << 24 | behind | (uint32_t)i << 19;
+            }
+            k0 += __popcll(c);
         }
     };
-    list(0);
+    if (cnt) {
+        if (tot <= kLinkCap) list(mk, 0, true);
+        else list(mk, 0, false);
+    }
+    bool landed = false;  // every pull of the tile has landed
     for (int base = 0; base < tot; base += kLinkCap) {
         if (base) {
             lds_barrier();  // the previous round's list is processed
-            list(base);
+            WaveMasks<TX> again;  // (not kept: few tiles need a second round)
+            wave_masks<TX>(reread(f), x0, wy, z, WaveRows<R>(wy, z, ny, nz), again);
+            list(again, base, false);
         }
         lds_barrier();  // the list is written (an LDS-only barrier: the pulls stay in flight)
         const int n = min(kLinkCap, tot - base);
-        for (int j = tid; j < n; j += kBlock) fused_link<S, TX, TY, TZ>(f, lds, x0, y0, z0, j, t);
+        for (int j0 = 0; j0 < n; j0 += kBlock) {
+            const int j = j0 + tid;
+            uint32_t bits = 0, it = 0;
+            if (j < n) {
+                it = lds.item[j];
+                bits = fused_link<S, TX, TY, TZ>(reread(f), src, lds, x0, y0, z0, it, t);
+            }
+            if (!landed) {
+                wait_vmem();
+                lds_barrier();
+                landed = true;
+            }
+            if (j < n) lds.val[(it >> 19) & 31u][it >> 24] = bits;
+        }
     }
     if (tot > 0) {
-        __syncthreads();  // the link values and the tile's body sums are complete
-        // 4. the tile's body sums, the copies added up
-        if (tid < kRec) {
-            const int key = lds.key[tid];
-            if (key >= 0) {
-                unsigned long long *gs = fix_slot(f, key, t);
+        lds_barrier();  // the link values and the tile's body sums are complete
+        // 4. the tile's body sums, the copies added up: one thread per body
+        //    and component, so that a body's six sums go out in one access
+        if (tid < 6 * kRec) {
+            const int slot = tid / 6, c = tid - 6 * slot;
+            const int key = lds.key[slot];
+            unsigned long long v = 0ull;
 #pragma unroll
-                for (int c = 0; c < 6; ++c) {
-                    unsigned long long v = 0ull;
-#pragma unroll
-                    for (int q = 0; q < kCopies; ++q) v += lds.sum[q][tid][c];
-                    if (v) atomicAdd(gs + c, v);
-                }
-            }
+            for (int q = 0; q < kCopies; ++q) v += lds.sum[q][slot][c];
+            if (key >= 0 && v) atomicAdd(fix_slot(f, key, t) + c, v);
         }
     }
 
     // 3. pull, collide and store (whole wavefronts; none with no fluid lane)
-    if (!in || __ballot(fluid) == 0) return;
+    if (!mk.fluid || !__builtin_amdgcn_inverse_ballot_w64(mk.in)) return;
+    const bool fluid = __builtin_amdgcn_inverse_ballot_w64(mk.fluid);
     float g[kQ];
     wait_vmem();  // this wavefront's pulls have landed in lds.val (the link values are there since the barrier)
     if (!fluid) {
@@ -383,8 +507,21 @@ __device__ __forceinline__ void fused_tile(const FusedArgs &f, int t, FusedLds &
 #pragma unroll
         for (int i = 0; i < kQ; ++i) g[i] = St::from_bits(lds.val[i][tid]);
     }
-    if (fluid && z == a.zieb_z) zieb_plane<S>(a, src, idx, g);
-    collide_store<S>(a, g, fluid, idx, dst);
+    f = reread(f);
+    StepArgs a;  // what the collision reads
+    a.Ns = f->s.Ns;
+    a.tau0 = f->s.tau0;
+    a.smag_k = f->s.smag_k;
+    a.rho0 = f->s.rho0;
+    a.fx = f->s.fx;
+    a.fy = f->s.fy;
+    a.fz = f->s.fz;
+    a.flag = f->s.flag;
+    a.zieb_state = f->s.zieb_state;
+    // index of the lane's node
+    const uint32_t idx = (uint32_t)x + (uint32_t)nx * ((uint32_t)y + (uint32_t)ny * (uint32_t)z);
+    if (inflow && fluid) zieb_plane<S>(a, src, idx, g);
+    collide_store<S>(a, g, fluid, idx, static_cast<T *>(dstv));
 }
 
 // Force entry i of a step (spheres, then walls) from its fixed-point sums,
@@ -421,7 +558,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) 
     if (f.fin.fsum)
         for (int i = blockIdx.x * kBlock + threadIdx.x; i < 6 * (f.fin.nb + f.fin.n_walls); i += gridDim.x * kBlock)
             finish_value(f.fin, i);
-    fused_tile<S, TX, TY, TZ>(f, xcd_remap(blockIdx.x, gridDim.x), lds);
+    // (f is the kernel's only argument: it lies at the segment's start)
+    const ArgPtr p = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    fused_tile<S, TX, TY, TZ>(p, f.s.src, f.s.dst, xcd_remap(blockIdx.x, gridDim.x), lds);
 }
 
 __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs fa)
@@ -455,7 +594,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6, 6))) 
     // the member of the previous tile is kept: a workgroup's next tile is
     // usually in the same member
     int mb = 0, me = 0;
-    FusedArgs f{};
+    ArgPtr f = nullptr;
+    const void *src = nullptr;
+    void *dst = nullptr;
     for (int k = 0;; ++k) {
         const int gt = xcd_item(xcd, __builtin_amdgcn_readfirstlane(next[k & 1]));
         if (gt >= b.total_tiles) break;  // the XCD's later items lie beyond too
@@ -469,16 +610,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6, 6))) 
                 if (b.members[mid].tile_begin <= gt) m = mid;
                 else top = mid;
             }
+            m = __builtin_amdgcn_readfirstlane(m);
             const BatchMember &bm = b.members[m];
             mb = bm.tile_begin;
             me = m + 1 < b.n ? b.members[m + 1].tile_begin : b.total_tiles;
-            FusedArgs t = bm.f;
-            const int c = b.cur[m];
-            t.s.src = bm.pop[c];
-            t.s.dst = bm.pop[c ^ 1];
-            f = uniform(t);
+            f = (ArgPtr)(uintptr_t)&bm.f;
+            const int c = __builtin_amdgcn_readfirstlane(b.cur[m]);
+            src = c ? bm.pop[1] : bm.pop[0];
+            dst = c ? bm.pop[0] : bm.pop[1];
         }
-        fused_tile<S, TX, TY, TZ>(f, gt - mb, lds);
+        fused_tile<S, TX, TY, TZ>(f, src, dst, gt - mb, lds);
         if (threadIdx.x == 0) next[(k + 1) & 1] = pre;
         lds_barrier();
     }

@@ -16,6 +16,7 @@
 // refilled for nothing: a solid node's populations are never read.
 #include "lbm_device.h"
 #include "lbm_internal.h"
+#include "lbm_linkmath.h"
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -50,6 +51,19 @@ __device__ __forceinline__ uint16_t cas_u16(uint16_t *addr, uint16_t expect, uin
     }
 }
 
+// The node turned from fluid to solid or back: its bit of the solid bitmap is
+// flipped, with its periodic copies at the row's ends.  Every change of a
+// node's owner is a compare-and-swap, so the changes of a node are in one
+// order and its flips add up to its final state, in whatever order they land.
+__device__ __forceinline__ void flip_bit(const GeomArgs &g, int px, int py, int pz)
+{
+    uint32_t *row = g.bits + (size_t)bit_row_words(g.nx) * ((size_t)py + (size_t)g.ny * pz);
+    auto flip = [&](int p) { atomicXor(row + (p >> 5), 1u << (p & 31)); };
+    flip(px + 1);
+    if (px == 0) flip(g.nx + 1);
+    if (px == g.nx - 1) flip(0);
+}
+
 // Sphere `id` (new geometry) takes node v, found with owner o.
 __device__ __forceinline__ void stamp_node(const GeomArgs &g, uint16_t *own, const Node &v, uint16_t o, uint16_t id)
 {
@@ -64,7 +78,10 @@ __device__ __forceinline__ void stamp_node(const GeomArgs &g, uint16_t *own, con
             }
         }
         const uint16_t prev = cas_u16(own + v.n, o, id);
-        if (prev == o) return;
+        if (prev == o) {
+            if (o >= kVacated) flip_bit(g, v.px, v.py, v.pz);
+            return;
+        }
         o = prev;
     }
 }
@@ -156,6 +173,33 @@ __global__ __launch_bounds__(kBlock) void k_walls_init(const uint8_t *wall, uint
     if (n < N) own[n] = wall[n] ? (uint16_t)(wall[n] - 1) : kFluid;
 }
 
+__global__ __launch_bounds__(kBlock) void k_link_records(GeomArgs g, const double *wrec)
+{
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= g.n_walls + g.nb) return;
+    static_cast<LinkRec *>(g.lrec)[i].k =
+        sphere_k(i < g.n_walls ? wrec + (size_t)i * kBodyStride : g.bodies + (size_t)(i - g.n_walls) * kBodyStride);
+}
+
+// The solid bitmap from the owner map: one thread per bit, two words per
+// wavefront from a ballot.  The bits of a row past its second periodic copy
+// are 0.
+__global__ __launch_bounds__(kBlock) void k_solid_bits(GeomArgs g)
+{
+    const int rw = bit_row_words(g.nx);
+    const size_t words = (size_t)rw * ((size_t)g.ny * (size_t)g.nz);
+    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    const size_t w = i >> 5, r = w / (size_t)rw;
+    const int p = (int)(w - r * (size_t)rw) * 32 + (int)(i & 31);
+    bool solid = false;
+    if (w < words && p <= g.nx + 1) {
+        const int x = p == 0 ? g.nx - 1 : (p == g.nx + 1 ? 0 : p - 1);
+        solid = g.own[(size_t)x + (size_t)g.nx * r] < kVacated;
+    }
+    const unsigned long long m = __ballot(solid);
+    if ((threadIdx.x & 31) == 0 && w < words) g.bits[w] = (uint32_t)(m >> (threadIdx.x & 32));
+}
+
 // Lattice coordinates of node index n (a rare path: integer divisions).
 __device__ __forceinline__ Node node_of(uint32_t n, int nx, int ny)
 {
@@ -190,6 +234,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     if (job < g.nb2) {
         // stamp: every node of the new ball not yet owned by the sphere
         const double *B = g.bodies2 + (size_t)job * kBodyStride;
+        if (lane == 0) static_cast<LinkRec *>(g.lrec)[g.n_walls + job].k = sphere_k(B);
         if (!body_ok(B, nx, ny, nz)) return;
         const uint16_t id = (uint16_t)(g.n_walls + job);
         const Box bx = body_box(B, 0);
@@ -269,6 +314,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             for (int u = 0; u < kColU; ++u) {
                 if (u >= cnt || o[u] != id || cas_u16(own + nn[u], id, kFluid) != id) continue;
                 const Node v = node_of(nn[u], nx, ny);
+                flip_bit(g, v.px, v.py, v.pz);
                 double u0, u1, u2;
                 sphere_velocity(B, v.px, v.py, v.pz, nx, ny, nz, u0, u1, u2);
                 for (int i = 0; i < kQ; ++i)
@@ -456,6 +502,21 @@ template <int S> struct MacroK { static constexpr auto fn = k_export_macro<S>; }
 hipError_t launch_walls_init(const uint8_t *wall, uint16_t *own, int N, hipStream_t s)
 {
     hipLaunchKernelGGL(k_walls_init, dim3(nblk(N)), dim3(kBlock), 0, s, wall, own, N);
+    return hipGetLastError();
+}
+
+hipError_t launch_link_records(const GeomArgs &g, const double *wrec, hipStream_t s)
+{
+    const int n = g.n_walls + g.nb;
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_link_records, dim3(nblk(n)), dim3(kBlock), 0, s, g, wrec);
+    return hipGetLastError();
+}
+
+hipError_t launch_solid_bits(const GeomArgs &g, hipStream_t s)
+{
+    const size_t bits = 32 * (size_t)bit_row_words(g.nx) * ((size_t)g.ny * (size_t)g.nz);
+    hipLaunchKernelGGL(k_solid_bits, dim3((unsigned)((bits + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, g);
     return hipGetLastError();
 }
 

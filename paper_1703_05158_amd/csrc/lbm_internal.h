@@ -18,10 +18,22 @@ constexpr uint16_t kVacated = 0x8000;
 constexpr int kMaxIds = 0x7FFE;
 
 constexpr int kBodyStride = 10;   // X[3], V[3], Omega[3], R
+constexpr int kLinkRecBytes = 64; // a solid's record for the links of the fused step
 constexpr int kWallStride = 6;    // U[3], ref[3]
 constexpr int kMaxWalls = 16;
 constexpr int kBlock = 256;       // threads of a workgroup
 constexpr int kWallChunk = 1024;  // wall links per workgroup of the link pass
+
+// Solid bitmap: one bit per node, 1 = solid (owner below kVacated), in rows of
+// x.  Row r = y + ny z starts at word r bit_row_words(nx); node x of the row
+// is bit x + 1, with the row's periodic neighbours beside it (bit 0 = node
+// nx - 1, bit nx + 1 = node 0), so that a wavefront reads the solid bits of a
+// run of nodes and of both x neighbours as one window, without wrapping.  A
+// window may reach into the next row (or past the last one: kBitPad words),
+// where its bits belong to no node of the wavefront.  With nx ny nz < 2^30 the
+// byte offset of a row stays below 2^32.
+inline __host__ __device__ int bit_row_words(int nx) { return (nx + 1) / 32 + 1; }
+constexpr int kBitPad = 2;
 
 // Tile shapes of the step kernel (256 nodes, one per thread).
 enum TileShape { kTile64x2x2 = 0, kTile32x4x2 = 1, kTile32x2x4 = 2, kTile16x8x2 = 3, kNumTileShapes = 4 };
@@ -119,12 +131,16 @@ struct FinishArgs {
 struct FusedArgs {
     StepArgs s;                   // the step (its wall-total fields unused)
     int n_walls, nb, halfway;
-    const double *bodies;         // [nb][kBodyStride], the current geometry
-    const double *wrec;           // [n_walls][kBodyStride]: each wall as a record {ref, U, 0, 0}
     unsigned long long *fsum;     // fixed-point sums: [max_bodies][6], then [n_walls][kWallRep][6]
     int wall_base;                // max_bodies: first wall copy of fsum
+    const void *lrec;             // LinkRec of every solid, by owner code
+    const uint32_t *bits;         // the solid bitmap of the geometry
+    uint32_t inv_ntx, inv_nty;    // quick_inv of the tile counts (the tile index is split without a division)
     FinishArgs fin;               // the previous step's sums (another buffer) to finish first, if fin.fsum
 };
+
+// t / d for t >= 0 as the high word of t quick_inv(d), at most one too small.
+inline uint32_t quick_inv(int d) { return d > 1 ? (uint32_t)((1ull << 32) / (uint64_t)d) : 0xFFFFFFFFu; }
 
 // One lattice of a batch: its fused-step arguments for the batch's tile
 // shape (src/dst filled in per step from pop[cur]), its force finish, and
@@ -178,6 +194,8 @@ struct GeomArgs {
     const double *bodies2;        // the new geometry's table, nb2 spheres
     int nb2;
     uint16_t *own;
+    uint32_t *bits;               // the solid bitmap, kept in step with own
+    void *lrec;                   // LinkRec of every solid, by owner code: the stamped spheres' are written
     void *pop;
     float rho0;
 };
@@ -209,6 +227,11 @@ hipError_t launch_adj_links(const AdjLinkArgs &g, hipStream_t s);
 hipError_t launch_adj_reduce(const double *dF_tile, int n_tiles, double *dF, hipStream_t s);
 
 hipError_t launch_walls_init(const uint8_t *wall, uint16_t *own, int N, hipStream_t s);
+// Link records of the walls (wrec: [n_walls][kBodyStride]) and of the spheres
+// of the current geometry (bodies, nb of g).
+hipError_t launch_link_records(const GeomArgs &g, const double *wrec, hipStream_t s);
+// The whole solid bitmap from the owner map (nx, ny, nz, own, bits of g).
+hipError_t launch_solid_bits(const GeomArgs &g, hipStream_t s);
 hipError_t launch_geometry(int storage, const GeomArgs &g, hipStream_t s);
 hipError_t launch_init_pop(int storage, const GeomArgs &g, const double *rho, const double *u,
                            hipStream_t s);

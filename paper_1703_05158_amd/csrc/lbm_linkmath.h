@@ -23,6 +23,14 @@ struct SphereK {
     float V0, V1, V2, W0, W1, W2, R2;
 };
 
+// The same as a record of 64 bytes, one per solid (walls first, then
+// spheres: indexed by owner code), made once per geometry: a link loads it
+// with four wide loads and converts nothing.
+struct alignas(64) LinkRec {
+    SphereK k;
+};
+static_assert(sizeof(LinkRec) == 64, "one 64-byte record");
+
 __device__ __forceinline__ SphereK sphere_k(const double *B)
 {
     SphereK k;
@@ -49,6 +57,9 @@ struct LinkGeo {
     float q, mw;
 };
 
+// All ones where direction i is an axis direction, else 0.
+__device__ __forceinline__ int axis_dir(int i) { return (int)__builtin_amdgcn_sbfe(0x1C0Eu, i, 1); }
+
 __device__ __forceinline__ LinkGeo link_geo(const SphereK &k, bool exact_q, bool sphere, float rho0, int x, int y,
                                             int z, int nx, int ny, int nz, int I)
 {
@@ -58,17 +69,24 @@ __device__ __forceinline__ LinkGeo link_geo(const SphereK &k, bool exact_q, bool
     l.d0 = (double)x - k.X0;
     l.d1 = (double)y - k.X1;
     l.d2 = (double)z - k.X2;
-    if (sphere) {
+    // the offset rounded once from FP64; q and the wall velocity in FP32
+    float e0 = (float)l.d0, e1 = (float)l.d1, e2 = (float)l.d2;
+    // the minimum image, where an offset is anywhere near half the box (few
+    // links are: one test, on the wide side, for the three axes)
+    if (sphere && ((__builtin_fabsf(e0) > 0.49f * (float)nx) | (__builtin_fabsf(e1) > 0.49f * (float)ny) |
+                   (__builtin_fabsf(e2) > 0.49f * (float)nz))) {
         l.d0 = min_image(l.d0, nx);
         l.d1 = min_image(l.d1, ny);
         l.d2 = min_image(l.d2, nz);
+        e0 = (float)l.d0;
+        e1 = (float)l.d1;
+        e2 = (float)l.d2;
     }
-    // the offset rounded once from FP64; q and the wall velocity in FP32
-    const float e0 = (float)l.d0, e1 = (float)l.d1, e2 = (float)l.d2;
+    const int axis = axis_dir(I);
     if (exact_q) {
         // smallest root in (0, 1] of |d + q c_K|^2 = R^2, cancellation-free form
         const float bb = -(e0 * cx + e1 * cy + e2 * cz);
-        const float aa = (float)(cx * cx + cy * cy + cz * cz);
+        const float aa = axis ? 1.0f : 2.0f;  // |c|^2
         const float cc = (e0 * e0 + e1 * e1 + e2 * e2) - k.R2;
         const float disc = fmaxf(bb * bb - aa * cc, 0.0f);
         // (the hardware square root and reciprocal, each within 1 ulp)
@@ -81,7 +99,7 @@ __device__ __forceinline__ LinkGeo link_geo(const SphereK &k, bool exact_q, bool
     const float u0 = k.V0 + (k.W1 * f2 - k.W2 * f1);
     const float u1 = k.V1 + (k.W2 * f0 - k.W0 * f2);
     const float u2 = k.V2 + (k.W0 * f1 - k.W1 * f0);
-    l.mw = (float)wgt(opp(I)) * rho0 * (cx * u0 + cy * u1 + cz * u2);
+    l.mw = (axis ? (float)(1.0 / 18.0) : (float)(1.0 / 36.0)) * rho0 * (cx * u0 + cy * u1 + cz * u2);
     return l;
 }
 
@@ -106,7 +124,7 @@ __device__ __forceinline__ float link_value(float q, float fk, float fa, float f
 __device__ __forceinline__ double link_momentum(float fk, float vr, int I, float rho0)
 {
 #pragma clang fp contract(off)
-    return (double)fk + (double)vr + 2.0 * wgt(I) * (double)rho0;
+    return (double)fk + (double)vr + (axis_dir(I) ? 2.0 * (1.0 / 18.0) : 2.0 * (1.0 / 36.0)) * (double)rho0;
 }
 
 // Force mom c_K on the body and its torque about the lever arm
@@ -115,15 +133,17 @@ __device__ __forceinline__ double link_momentum(float fk, float vr, int I, float
 __device__ __forceinline__ void link_force_terms(double mom, int I, const LinkGeo &l, double (&t)[6])
 {
 #pragma clang fp contract(off)
-    const int cx = dcx(I), cy = dcy(I), cz = dcz(I);
-    const double a0 = l.d0, a1 = l.d1, a2 = l.d2;
-    const double F0 = -mom * cx, F1 = -mom * cy, F2 = -mom * cz;
-    t[0] = F0;
-    t[1] = F1;
-    t[2] = F2;
-    t[3] = a1 * F2 - a2 * F1;
-    t[4] = a2 * F0 - a0 * F2;
-    t[5] = a0 * F1 - a1 * F0;
+    // the components of c are -1, 0 or 1: products with them are exact, so
+    // a x F is taken from the three products a mom, and the fused
+    // multiply-adds round once, as the difference of two products would
+    const double cx = dcx(I), cy = dcy(I), cz = dcz(I);
+    const double m0 = l.d0 * mom, m1 = l.d1 * mom, m2 = l.d2 * mom;
+    t[0] = -mom * cx;
+    t[1] = -mom * cy;
+    t[2] = -mom * cz;
+    t[3] = __builtin_fma(m2, cy, -(m1 * cz));
+    t[4] = __builtin_fma(m0, cz, -(m2 * cx));
+    t[5] = __builtin_fma(m1, cx, -(m0 * cy));
 }
 
 // The same terms added to acc[6].
