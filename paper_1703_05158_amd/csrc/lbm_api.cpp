@@ -34,6 +34,8 @@ struct lbm_ctx {
     int cur = 0;                       // pop[cur] holds the current (post-collision) state
     uint16_t *own = nullptr;
     uint32_t *bits = nullptr;          // solid bitmap of own (bit_row_words)
+    int *lost = nullptr;               // 3 * max_bodies: marks of the geometry updates, in turn (GeomArgs)
+    int lost_cur = 0;                  // which third the last update marked
     void *lrec = nullptr;              // (max_walls + max_bodies) * kLinkRecBytes: link records by owner code
     uint8_t *wall_map = nullptr;
     double *tab[2] = {nullptr, nullptr};
@@ -117,6 +119,12 @@ lbm_status fail(lbm_ctx *h, lbm_status st, const char *fmt, ...)
         if (e_ != hipSuccess)                                                                    \
             return fail((h), e_ == hipErrorOutOfMemory ? LBM_ERR_OOM : LBM_ERR_HIP, "%s: %s (%s)", \
                         #expr, hipGetErrorString(e_), hipGetErrorName(e_));                      \
+    } while (0)
+
+#define TRY(expr)                        \
+    do {                                 \
+        lbm_status st_ = (expr);         \
+        if (st_ != LBM_OK) return st_;   \
     } while (0)
 
 bool finite_all(const double *p, size_t n)
@@ -339,6 +347,19 @@ lbm_status upload_wall_records(lbm_ctx *h, const double *wt, int n)
     return LBM_OK;
 }
 
+// One geometry update: the marks move on by one.
+lbm_status update_geometry(lbm_ctx *h, GeomArgs &g)
+{
+    const size_t cap = (size_t)std::max(h->cfg.max_bodies, 1);
+    const int prev = h->lost_cur, cur = (prev + 1) % 3, next = (prev + 2) % 3;
+    h->lost_cur = cur;
+    g.lost_prev = h->lost + prev * cap;
+    g.lost = h->lost + cur * cap;
+    g.lost_next = h->lost + next * cap;
+    HIP_TRY(h, launch_geometry(h->cfg.storage, g, h->stream));
+    return LBM_OK;
+}
+
 // Rebuild the whole owner map: walls, then the spheres of tab[ts].
 lbm_status rasterize_full(lbm_ctx *h)
 {
@@ -348,7 +369,7 @@ lbm_status rasterize_full(lbm_ctx *h)
     g.nb2 = g.nb;
     g.nb = 0;
     HIP_TRY(h, launch_walls_init(h->wall_map, h->own, h->N, h->stream));
-    HIP_TRY(h, launch_geometry(h->cfg.storage, g, h->stream));
+    TRY(update_geometry(h, g));
     HIP_TRY(h, launch_solid_bits(g, h->stream));
     return LBM_OK;
 }
@@ -360,7 +381,7 @@ lbm_status rasterize_update(lbm_ctx *h)
     GeomArgs g = geom(h);
     g.bodies2 = h->tab[1 - h->ts];
     g.nb2 = h->nb_next;
-    HIP_TRY(h, launch_geometry(h->cfg.storage, g, h->stream));
+    TRY(update_geometry(h, g));
     h->ts = 1 - h->ts;
     h->nb_state = h->nb_next;
     h->dirty = false;
@@ -454,12 +475,6 @@ struct EventPair {
         if (e1) (void)hipEventDestroy(e1);
     }
 };
-
-#define TRY(expr)                        \
-    do {                                 \
-        lbm_status st_ = (expr);         \
-        if (st_ != LBM_OK) return st_;   \
-    } while (0)
 
 void free_wall_links(lbm_ctx *h)
 {
@@ -582,6 +597,7 @@ lbm_status lbm_create(const lbm_config *cfg, lbm_handle *out)
         dalloc(h, &h->own, sizeof(uint16_t) * N + 4) != hipSuccess ||
         dalloc(h, &h->bits, sizeof(uint32_t) * (bit_row_words(c.nx) * ((size_t)c.ny * (size_t)c.nz) + kBitPad)) !=
             hipSuccess ||
+        dalloc(h, &h->lost, sizeof(int) * 3 * (size_t)std::max(c.max_bodies, 1)) != hipSuccess ||
         dalloc(h, &h->lrec, (size_t)kLinkRecBytes * std::max(nbt, 1)) != hipSuccess ||
         dalloc(h, &h->wall_map, (size_t)N) != hipSuccess ||
         dalloc(h, &h->tab[0], sizeof(double) * kBodyStride * std::max(c.max_bodies, 1)) != hipSuccess ||
@@ -604,6 +620,7 @@ lbm_status lbm_create(const lbm_config *cfg, lbm_handle *out)
         return bail(LBM_ERR_OOM);
     if (hipEventCreateWithFlags(&h->stage_evt, hipEventDisableTiming) != hipSuccess) return bail(LBM_ERR_HIP);
     if (hipMemsetAsync(h->wall_map, 0, (size_t)N, h->stream) != hipSuccess ||
+        hipMemsetAsync(h->lost, 0, sizeof(int) * 3 * (size_t)std::max(c.max_bodies, 1), h->stream) != hipSuccess ||
         hipMemsetAsync(h->pop[0], 0, popb, h->stream) != hipSuccess ||
         hipMemsetAsync(h->pop[1], 0, popb, h->stream) != hipSuccess ||
         hipMemsetAsync(h->acc, 0, sizeof(double) * 6 * std::max(nbt, 1), h->stream) != hipSuccess ||
@@ -626,7 +643,7 @@ void lbm_destroy(lbm_handle h)
     (void)hipStreamSynchronize(h->stream);
     for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
     free_wall_links(h);
-    void *dev[] = {h->pop[0], h->pop[1], h->own, h->bits, h->lrec, h->wall_map, h->tab[0], h->tab[1], h->walls, h->wrec,
+    void *dev[] = {h->pop[0], h->pop[1], h->own, h->bits, h->lost, h->lrec, h->wall_map, h->tab[0], h->tab[1], h->walls, h->wrec,
                    h->acc, h->fsum[0], h->fsum[1], h->order, h->flag, h->scratch, h->zstate, h->zpart};
     for (void *p : dev)
         if (p) (void)hipFree(p);
@@ -1150,6 +1167,9 @@ lbm_status lbm_set_state(lbm_handle h, const void *buf, size_t bytes)
     h->dirty = hd.dirty != 0;
     h->steps_done = hd.steps_done;
     HIP_TRY(h, launch_solid_bits(geom(h), h->stream));
+    // which spheres own all of their balls is not part of a checkpoint
+    HIP_TRY(h, launch_mark_all(h->lost + h->lost_cur * (size_t)std::max(h->cfg.max_bodies, 1), h->cfg.max_bodies,
+                               h->stream));
     HIP_TRY(h, launch_link_records(geom(h), h->wrec, h->stream));
     h->initialized = true;
     h->geom_gen++;

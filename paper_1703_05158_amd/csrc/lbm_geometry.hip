@@ -1,17 +1,21 @@
 // Owner-map maintenance and state import/export kernels (gfx950).
 //
 // The owner map is kept incrementally when spheres move, in one launch with
-// one wavefront per new sphere and one per old sphere, in any order:
-//  - stamp: sphere c takes every node of its new ball unless a wall or a
-//    lower-index sphere whose new ball also covers it owns the node; it takes
-//    the node by compare-and-swap from any other owner (a higher index, the
-//    fluid, or a lower index that is leaving the node);
-//  - vacate: a node the previous geometry's sphere a owned and its new ball
-//    does not cover turns fluid by compare-and-swap from a, if no sphere has
-//    taken it, and is refilled with the equilibrium at rho0 and the velocity
-//    it had as a solid (the solid-side Maxwell equilibrium of Sec. 2.3).
+// one wavefront per sphere, in any order:
+//  - the sphere enters the nodes of its new ball that its old one did not
+//    cover: it takes each unless a wall or a lower-index sphere whose new ball
+//    also covers it owns it, by compare-and-swap from any other owner (a
+//    higher index, the fluid, or a lower index that is leaving the node);
+//  - it leaves the nodes of its old ball that its new one does not cover:
+//    those it still owns turn fluid by compare-and-swap, and are refilled with
+//    the equilibrium at rho0 and the velocity they had as a solid (the
+//    solid-side Maxwell equilibrium of Sec. 2.3).
+// A node in both balls needs a look only where balls overlap: a sphere that
+// was refused a node of its ball, or lost one, is marked, and a marked sphere
+// goes through its whole new ball in the next update.  An unmarked sphere owns
+// every node of its ball that is not a wall's.
 // Every node ends with the owner of the new geometry whatever the order of
-// the workgroups: the lowest-index sphere whose new ball covers it (walls
+// the wavefronts: the lowest-index sphere whose new ball covers it (walls
 // first), else fluid.  A node refilled and then taken by another sphere was
 // refilled for nothing: a solid node's populations are never read.
 #include "lbm_device.h"
@@ -64,8 +68,14 @@ __device__ __forceinline__ void flip_bit(const GeomArgs &g, int px, int py, int 
     if (px == g.nx - 1) flip(0);
 }
 
+// Sphere b is marked: it may not own every node of its new ball.
+__device__ __forceinline__ void mark(const GeomArgs &g, int b)
+{
+    __hip_atomic_store(g.lost + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Sphere `id` (new geometry) takes node v, found with owner o.
-__device__ __forceinline__ void stamp_node(const GeomArgs &g, uint16_t *own, const Node &v, uint16_t o, uint16_t id)
+__device__ __forceinline__ void enter_node(const GeomArgs &g, const Node &v, uint16_t o, uint16_t id)
 {
     while (true) {
         if (o < g.n_walls || o == id) return;
@@ -74,12 +84,16 @@ __device__ __forceinline__ void stamp_node(const GeomArgs &g, uint16_t *own, con
             const int b = o - g.n_walls;
             if (b < g.nb2) {
                 const double *Bo = g.bodies2 + (size_t)b * kBodyStride;
-                if (body_ok(Bo, g.nx, g.ny, g.nz) && inside(Bo, v.px, v.py, v.pz, g.nx, g.ny, g.nz)) return;
+                if (body_ok(Bo, g.nx, g.ny, g.nz) && inside(Bo, v.px, v.py, v.pz, g.nx, g.ny, g.nz)) {
+                    mark(g, id - g.n_walls);
+                    return;
+                }
             }
         }
-        const uint16_t prev = cas_u16(own + v.n, o, id);
+        const uint16_t prev = cas_u16(g.own + v.n, o, id);
         if (prev == o) {
             if (o >= kVacated) flip_bit(g, v.px, v.py, v.pz);
+            else if (o > id && o - g.n_walls < g.nb2) mark(g, o - g.n_walls);
             return;
         }
         o = prev;
@@ -164,9 +178,6 @@ __device__ __forceinline__ void column_range(const double *B, const Box &bx, con
     while (hi >= lo && !inside(B, px, py, wrap1(hi, nz), nx, ny, nz)) --hi;
 }
 
-constexpr int kColU = 8;         // nodes of a lane whose owner loads are in flight together
-constexpr int kColsPerLane = 4;  // columns of a stamp lane whose nodes are taken together
-
 __global__ __launch_bounds__(kBlock) void k_walls_init(const uint8_t *wall, uint16_t *own, int N)
 {
     const int n = blockIdx.x * kBlock + threadIdx.x;
@@ -179,6 +190,12 @@ __global__ __launch_bounds__(kBlock) void k_link_records(GeomArgs g, const doubl
     if (i >= g.n_walls + g.nb) return;
     static_cast<LinkRec *>(g.lrec)[i].k =
         sphere_k(i < g.n_walls ? wrec + (size_t)i * kBodyStride : g.bodies + (size_t)(i - g.n_walls) * kBodyStride);
+}
+
+__global__ __launch_bounds__(kBlock) void k_mark_all(int *lost, int n)
+{
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    if (i < n) lost[i] = 1;
 }
 
 // The solid bitmap from the owner map: one thread per bit, two words per
@@ -207,154 +224,222 @@ __device__ __forceinline__ Node node_of(uint32_t n, int nx, int ny)
     return Node{(int)(r % (uint32_t)nx), (int)(r / (uint32_t)nx), (int)(n / plane), n};
 }
 
-// One wavefront per job: jobs 0 .. nb2 - 1 stamp new sphere b, jobs nb2 ..
-// nb2 + nb - 1 vacate old sphere b, all in any order.  The lanes take the
-// (x, y) columns of the sphere's box, kColsPerLane at a time; each column's
-// range of ball nodes comes from column_range, and the owner codes of a
-// lane's nodes are loaded kColU at a time across its columns, so that a job
-// waits for few memory round trips.
+// Position of wrapped coordinate p in a box that starts at x0 (the image
+// nearest its origin).
+__device__ __forceinline__ int box_pos(int p, int x0, int n)
+{
+    const int k = p - x0;
+    return k < 0 ? k + n : (k >= n ? k - n : k);
+}
+
+constexpr int kGeomList = 192;  // changed nodes of a wavefront taken together
+
+// The n listed nodes of a wavefront change hands: sphere `id` enters or leaves
+// them.  Returns 0, the new length of the list.
 template <int S>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_geometry(GeomArgs g)
+__device__ __forceinline__ int work_off(const GeomArgs &g, const uint32_t *list, int n, uint16_t id,
+                                        const double *bodies, int lane)
 {
     using St = Store<S>;
-    __shared__ uint32_t cand[kColU][kBlock];  // vacate: a lane's leaving nodes, flushed kColU at a time
-    // the job is the same on every lane of the wavefront: made uniform, so that
-    // its sphere records are scalar loads
-    const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / 64) + (int)(threadIdx.x >> 6));
-    if (w >= g.nb + g.nb2) return;
-    // stamp and vacate jobs alternate while both last (the two kinds cost
-    // differently); job < nb2 stamps sphere job, else vacates job - nb2
-    const int mb = min(g.nb, g.nb2);
-    const int job = w < 2 * mb ? ((w & 1) ? g.nb2 + (w >> 1) : (w >> 1))
-                               : (g.nb2 > g.nb ? w - mb : g.nb2 + (w - mb));
-    const int lane = threadIdx.x & 63, tid = threadIdx.x;
+    typename St::T *pop = static_cast<typename St::T *>(g.pop);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+    for (int k0 = 0; k0 < n; k0 += 64) {
+        bool left = false;
+        if (k0 + lane < n) {
+            const uint32_t e = list[k0 + lane], node = e & 0x7FFFFFFFu;
+            const uint16_t o = g.own[node];
+            const Node v = node_of(node, g.nx, g.ny);
+            if (!(e >> 31)) {
+                enter_node(g, v, o, id);
+            } else if (o == id && cas_u16(g.own + node, id, kFluid) == id) {
+                flip_bit(g, v.px, v.py, v.pz);
+                left = true;
+            }
+        }
+        // refill: three nodes at a time, 19 lanes each
+#pragma unroll 1
+        for (uint64_t m = __ballot(left); m;) {
+            const int i = lane % kQ, third = lane / kQ;
+            int from = -1;
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                if (third == t && m) from = __builtin_ctzll(m);
+                m &= m - 1;
+            }
+            if (from >= 0) {
+                const Node v = node_of(list[k0 + from] & 0x7FFFFFFFu, g.nx, g.ny);
+                double u0, u1, u2;
+                sphere_velocity(bodies + (size_t)(id - g.n_walls) * kBodyStride, v.px, v.py, v.pz, g.nx, g.ny, g.nz, u0,
+                                u1, u2);
+                St::st(at(pop + (size_t)i * g.Ns, v.n), (float)eq_dev(i, g.rho0, u0, u1, u2));
+            }
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    return 0;
+}
+
+// The value of lane `l` (compile-time or uniform) on every lane, as a scalar.
+__device__ __forceinline__ int lane_of(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ __forceinline__ float lane_of(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+// One wavefront per sphere.  The lanes take the (x, y) columns of the new
+// ball's box, then those of the old ball's that lie beside it; the ends of a
+// column's new and old ranges give the nodes the sphere enters and leaves
+// there, which are listed in LDS.  The list is worked off by the whole
+// wavefront: one lane per node for the owner's compare-and-swap, then one lane
+// per direction for the refills.
+// What bounds it: one wavefront's chain of sphere record, column ranges, owner
+// and compare-and-swap, through code that the step kernel's stream has pushed
+// out of the caches; hence one copy of each part, the two balls side by side
+// on two lanes, and no look at nodes that stay.  128x128x512 duct, 4000
+// spheres, about one changed node per sphere: 19.7 us; one wavefront per stamp
+// and one per vacate, each looking at every node of its ball, took 25.3 us
+// (12.1 against 11.0 us with 90 spheres, where one chain is all there is).
+template <int S>
+__global__ __launch_bounds__(kBlock) void k_geometry(GeomArgs g)
+{
+    __shared__ uint32_t lists[kBlock / 64][kGeomList];  // node index, bit 31: left by the sphere
+    // the sphere is the same on every lane of the wavefront: made uniform, so
+    // that what follows from it is scalar
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int b = (int)blockIdx.x * (kBlock / 64) + wv;
+    if (b >= max(g.nb, g.nb2)) return;
+    const int lane = threadIdx.x & 63;
     const int nx = g.nx, ny = g.ny, nz = g.nz;
     const uint32_t plane = (uint32_t)nx * (uint32_t)ny;
-    uint16_t *own = g.own;
-    if (job < g.nb2) {
-        // stamp: every node of the new ball not yet owned by the sphere
-        const double *B = g.bodies2 + (size_t)job * kBodyStride;
-        if (lane == 0) static_cast<LinkRec *>(g.lrec)[g.n_walls + job].k = sphere_k(B);
-        if (!body_ok(B, nx, ny, nz)) return;
-        const uint16_t id = (uint16_t)(g.n_walls + job);
-        const Box bx = body_box(B, 0);
-        const BallCols bc = ball_cols(B, bx);
-        const int ncols = bx.ex * bx.ey;
-        for (int cb = 0; cb < ncols; cb += 64 * kColsPerLane) {
-            // the lane's columns: first z, node count, column index
-            int lo[kColsPerLane], cum[kColsPerLane + 1];
-            uint32_t cx[kColsPerLane];
-            cum[0] = 0;
+    uint32_t *list = lists[wv];
+    const uint16_t id = (uint16_t)(g.n_walls + b);
+    // even lanes set up the new ball, odd lanes the old one
+    const bool mine = (lane & 1) == 0 ? b < g.nb2 : b < g.nb;
+    const double *table[2] = {g.bodies2, g.bodies};
+    const double *B = (lane & 1 ? g.bodies : g.bodies2) + (mine ? (size_t)b * kBodyStride : (size_t)0);
+    const int lost = b < g.nb ? g.lost_prev[b] : 0;
+    const int ok = mine && body_ok(B, nx, ny, nz);
+    const Box bx = body_box(B, 0);
+    const BallCols bc = ball_cols(B, bx);
+    const int inv = (int)(0xFFFFFFFFu / (uint32_t)max(bx.ex, 1));
+    int in_ball[2];
+    Box box[2];
+    BallCols cols[2];
+    uint32_t invs[2];
 #pragma unroll
-            for (int j = 0; j < kColsPerLane; ++j) {
-                const int c = cb + j * 64 + lane;
-                int l = 1, h = 0;
-                cx[j] = 0;
-                if (c < ncols) {
-                    const int ky = c / bx.ex, kx = c - ky * bx.ex;
-                    const int px = wrap1(bx.x0 + kx, nx), py = wrap1(bx.y0 + ky, ny);
-                    column_range(B, bx, bc, kx, ky, px, py, nx, ny, nz, l, h);
-                    cx[j] = (uint32_t)(px + nx * py);
-                }
-                lo[j] = l;
-                cum[j + 1] = cum[j] + max(h - l + 1, 0);
+    for (int t = 0; t < 2; ++t) {
+        in_ball[t] = lane_of(ok, t);
+        box[t] = Box{lane_of(bx.x0, t), lane_of(bx.y0, t), lane_of(bx.z0, t),
+                     lane_of(bx.ex, t), lane_of(bx.ey, t), lane_of(bx.ez, t)};
+        cols[t] = BallCols{lane_of(bc.ox, t), lane_of(bc.oy, t), lane_of(bc.oz, t),
+                           lane_of(bc.r2, t), lane_of(bc.eps2, t), lane_of(bc.m, t)};
+        invs[t] = (uint32_t)lane_of(inv, t);
+    }
+    // a marked sphere goes through its whole new ball
+    const bool whole = __builtin_amdgcn_readfirstlane(lost) != 0;
+    if (lane == 0) {
+        g.lost_next[b] = 0;
+        if (mine) static_cast<LinkRec *>(g.lrec)[g.n_walls + b].k = sphere_k(B);
+    }
+    const int n_new = in_ball[0] ? box[0].ex * box[0].ey : 0;
+    const int n_cols = n_new + (in_ball[1] ? box[1].ex * box[1].ey : 0);
+    int n = 0;  // listed nodes
+    for (int c0 = 0; c0 < n_cols; c0 += 64) {
+        // ---- 64 columns: the changed nodes of each
+        int e1 = 0, e2 = 0, l1 = 0, l2 = 0;                   // nodes entered and left: two runs of each
+        int ze1 = 0, ze2 = 0, zl1 = 0, zl2 = 0;               // their first z (unwrapped)
+        int start[2] = {0, 0}, len[2] = {0, 0};               // the column's ranges: wrapped start, length
+        bool every = true;                                    // the runs are exactly the changed nodes
+        uint32_t col = 0;
+        const int c = c0 + lane;
+        if (c < n_cols) {
+            const int t0 = c >= n_new, cc = t0 ? c - n_new : c;
+            const int ex = t0 ? box[1].ex : box[0].ex;
+            int ky = (int)__umulhi((uint32_t)cc, t0 ? invs[1] : invs[0]), kx = cc - ky * ex;
+            if (kx >= ex) {
+                ++ky;
+                kx -= ex;
             }
-            // the lane's nodes k = 0 .. cum[kColsPerLane] - 1, column by column
-            for (int k0 = 0; k0 < cum[kColsPerLane]; k0 += kColU) {
-                uint32_t nn[kColU];
-                unsigned todo = 0;
+            const int px = wrap1((t0 ? box[1].x0 : box[0].x0) + kx, nx), py = wrap1((t0 ? box[1].y0 : box[0].y0) + ky, ny);
+            col = (uint32_t)px + (uint32_t)nx * (uint32_t)py;
+            int a[2], e[2];
 #pragma unroll
-                for (int u = 0; u < kColU; ++u) {
-                    const int k = k0 + u;
-                    int z = lo[0] + k;
-                    uint32_t col = cx[0];
-#pragma unroll
-                    for (int j = 1; j < kColsPerLane; ++j)
-                        if (k >= cum[j]) {
-                            z = lo[j] + (k - cum[j]);
-                            col = cx[j];
+            for (int t = 0; t < 2; ++t) {
+                a[t] = 1;
+                e[t] = 0;
+            }
+            const bool in_new = in_ball[0] && box_pos(px, box[0].x0, nx) < box[0].ex && box_pos(py, box[0].y0, ny) < box[0].ey;
+            if (!(t0 && in_new)) {  // (an old column inside the new box was taken with the new ones)
+#pragma unroll 1
+                for (int t = t0; t < 2; ++t) {
+                    const Box &bt = t ? box[1] : box[0];
+                    const int qx = box_pos(px, bt.x0, nx), qy = box_pos(py, bt.y0, ny);
+                    if ((t ? in_ball[1] : in_ball[0]) && qx < bt.ex && qy < bt.ey) {
+                        int lo, hi;
+                        column_range(table[t] + (size_t)b * kBodyStride, bt, t ? cols[1] : cols[0], qx, qy, px, py, nx, ny,
+                                     nz, lo, hi);
+                        if (t) {
+                            a[1] = lo;
+                            e[1] = max(hi, lo - 1);
+                        } else {
+                            a[0] = lo;
+                            e[0] = max(hi, lo - 1);
                         }
-                    nn[u] = col + plane * (uint32_t)wrap1(z, nz);
-                    if (k < cum[kColsPerLane] && own[nn[u]] != id) todo |= 1u << u;
-                }
-                // the nodes not yet the sphere's (few: most were already)
-                while (todo) {
-                    const int u = __builtin_ctz(todo);
-                    todo &= todo - 1;
-                    uint32_t n = nn[0];
-#pragma unroll
-                    for (int v = 1; v < kColU; ++v)
-                        if (u == v) n = nn[v];
-                    stamp_node(g, own, node_of(n, nx, ny), own[n], id);
+                    }
                 }
             }
-        }
-    } else if (job < g.nb2 + g.nb) {
-        // vacate: nodes of the old ball outside the new one that the sphere
-        // still owns turn fluid (unless another sphere takes them first) and
-        // are refilled
-        const int b = job - g.nb2;
-        const double *B = g.bodies + (size_t)b * kBodyStride;
-        if (!body_ok(B, nx, ny, nz)) return;
-        typename St::T *pop = static_cast<typename St::T *>(g.pop);
-        const double *Bn = g.bodies2 + (size_t)b * kBodyStride;
-        const bool keeps = b < g.nb2 && body_ok(Bn, nx, ny, nz);
-        const uint16_t id = (uint16_t)(g.n_walls + b);
-        const Box bx = body_box(B, 0);
-        int cnt = 0;
-        auto flush = [&]() {
-            uint32_t nn[kColU];
-            uint16_t o[kColU];
 #pragma unroll
-            for (int u = 0; u < kColU; ++u) {
-                nn[u] = u < cnt ? cand[u][tid] : 0u;
-                o[u] = u < cnt ? own[nn[u]] : (uint16_t)0;
+            for (int t = 0; t < 2; ++t) {
+                start[t] = wrap1(a[t], nz);
+                len[t] = e[t] - a[t] + 1;
             }
-#pragma unroll
-            for (int u = 0; u < kColU; ++u) {
-                if (u >= cnt || o[u] != id || cas_u16(own + nn[u], id, kFluid) != id) continue;
-                const Node v = node_of(nn[u], nx, ny);
-                flip_bit(g, v.px, v.py, v.pz);
-                double u0, u1, u2;
-                sphere_velocity(B, v.px, v.py, v.pz, nx, ny, nz, u0, u1, u2);
-                for (int i = 0; i < kQ; ++i)
-                    St::st(at(pop + (size_t)i * g.Ns, v.n), (float)eq_dev(i, g.rho0, u0, u1, u2));
+            // the old range in the new one's frame, at the nearest image:
+            // ranges of at most half the axis each meet at no other image
+            int d = start[1] - start[0];
+            if (2 * d > nz) d -= nz;
+            else if (2 * d <= -nz) d += nz;
+            const int oa = a[0] + d, oe = oa + len[1] - 1;
+            every = 2 * len[0] <= nz && 2 * len[1] <= nz;
+            ze1 = a[0];
+            zl1 = oa;
+            if (!every) {  // all of both ranges, each node then tested against the other
+                e1 = len[0];
+                l1 = len[1];
+            } else {
+                ze2 = max(a[0], oe + 1);
+                zl2 = max(oa, e[0] + 1);
+                e1 = max(0, min(e[0], oa - 1) - ze1 + 1);
+                e2 = max(0, e[0] - ze2 + 1);
+                l1 = max(0, min(oe, a[0] - 1) - zl1 + 1);
+                l2 = max(0, oe - zl2 + 1);
             }
-            cnt = 0;
-        };
-        const BallCols bc = ball_cols(B, bx);
-        Box bxn{};
-        BallCols bcn{};
-        if (keeps) {
-            bxn = body_box(Bn, 0);
-            bcn = ball_cols(Bn, bxn);
-        }
-        for (int c = lane; c < bx.ex * bx.ey; c += 64) {
-            const int ky = c / bx.ex, kx = c - ky * bx.ex;
-            const int px = wrap1(bx.x0 + kx, nx), py = wrap1(bx.y0 + ky, ny);
-            int lo, hi, nlo = 1, nhi = 0;
-            column_range(B, bx, bc, kx, ky, px, py, nx, ny, nz, lo, hi);
-            if (lo > hi) continue;
-            if (keeps) {
-                // the column's position in the new ball's box (the image nearest its origin)
-                int kxn = px - bxn.x0, kyn = py - bxn.y0;
-                if (kxn < 0) kxn += nx; else if (kxn >= nx) kxn -= nx;
-                if (kyn < 0) kyn += ny; else if (kyn >= ny) kyn -= ny;
-                if (kxn < bxn.ex && kyn < bxn.ey) column_range(Bn, bxn, bcn, kxn, kyn, px, py, nx, ny, nz, nlo, nhi);
-            }
-            // the new range as a periodic interval of wrapped z: start ns, length nlen
-            const int ns = wrap1(nlo, nz), nlen = max(nhi - nlo + 1, 0);
-            const uint32_t col = (uint32_t)(px + nx * py);
-            for (int vz = lo; vz <= hi; ++vz) {
-                const int pz = wrap1(vz, nz);
-                int d = pz - ns;
-                if (d < 0) d += nz;
-                if (d < nlen) continue;  // stays in the ball
-                cand[cnt][tid] = col + plane * (uint32_t)pz;
-                if (++cnt == kColU) flush();
+            if (whole) {
+                e1 = len[0];
+                e2 = 0;
             }
         }
-        if (cnt) flush();
+        // ---- listed, one node of each column at a time
+        const int cnt = e1 + e2 + l1 + l2;
+        for (int k = 0;; ++k) {
+            // ---- the listed nodes change hands when the list is full or
+            //      there are no more
+            const bool more = __ballot(k < cnt) != 0;
+            if (n > kGeomList - 64 || (!more && n && c0 + 64 >= n_cols)) n = work_off<S>(g, list, n, id, g.bodies, lane);
+            if (!more) break;
+            const bool leaves = k >= e1 + e2;
+            const int z = k < e1 ? ze1 + k
+                                 : (!leaves ? ze2 + (k - e1) : (k < e1 + e2 + l1 ? zl1 + (k - e1 - e2) : zl2 + (k - e1 - e2 - l1)));
+            const int pz = wrap1(z, nz);
+            bool changed = k < cnt;
+            if (!every && changed && (leaves || !whole))
+                changed = box_pos(pz, leaves ? start[0] : start[1], nz) >= (leaves ? len[0] : len[1]);
+            const uint64_t m = __ballot(changed);
+            if (changed)
+                list[n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+                    (col + plane * (uint32_t)pz) | (leaves ? 0x80000000u : 0u);
+            n += __popcll(m);
+        }
     }
 }
 
@@ -513,6 +598,13 @@ hipError_t launch_link_records(const GeomArgs &g, const double *wrec, hipStream_
     return hipGetLastError();
 }
 
+hipError_t launch_mark_all(int *lost, int n, hipStream_t s)
+{
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_mark_all, dim3(nblk(n)), dim3(kBlock), 0, s, lost, n);
+    return hipGetLastError();
+}
+
 hipError_t launch_solid_bits(const GeomArgs &g, hipStream_t s)
 {
     const size_t bits = 32 * (size_t)bit_row_words(g.nx) * ((size_t)g.ny * (size_t)g.nz);
@@ -522,9 +614,9 @@ hipError_t launch_solid_bits(const GeomArgs &g, hipStream_t s)
 
 hipError_t launch_geometry(int storage, const GeomArgs &g, hipStream_t s)
 {
-    const int jobs = g.nb + g.nb2;
-    if (jobs <= 0) return hipSuccess;
-    const int grid = (jobs + kBlock / 64 - 1) / (kBlock / 64);
+    const int spheres = std::max(g.nb, g.nb2);
+    if (spheres <= 0) return hipSuccess;
+    const int grid = (spheres + kBlock / 64 - 1) / (kBlock / 64);
     return dispatch<GeomK>(storage, dim3(grid), dim3(kBlock), s, g);
 }
 

@@ -195,7 +195,12 @@ struct GeomArgs {
     int nb2;
     uint16_t *own;
     uint32_t *bits;               // the solid bitmap, kept in step with own
-    void *lrec;                   // LinkRec of every solid, by owner code: the stamped spheres' are written
+    void *lrec;                   // LinkRec of every solid, by owner code: the new spheres' are written
+    // marks of the spheres that may not own every node of their ball (0 or
+    // 1): of the previous update (read), of this one (0 at its start) and of
+    // the next (cleared)
+    const int *lost_prev;
+    int *lost, *lost_next;
     void *pop;
     float rho0;
 };
@@ -231,6 +236,7 @@ hipError_t launch_walls_init(const uint8_t *wall, uint16_t *own, int N, hipStrea
 // of the current geometry (bodies, nb of g).
 hipError_t launch_link_records(const GeomArgs &g, const double *wrec, hipStream_t s);
 // The whole solid bitmap from the owner map (nx, ny, nz, own, bits of g).
+hipError_t launch_mark_all(int *lost, int n, hipStream_t s);
 hipError_t launch_solid_bits(const GeomArgs &g, hipStream_t s);
 hipError_t launch_geometry(int storage, const GeomArgs &g, hipStream_t s);
 hipError_t launch_init_pop(int storage, const GeomArgs &g, const double *rho, const double *u,
