@@ -89,12 +89,17 @@ __device__ __forceinline__ void acc_first(float &s, bool &first, float t)
 // values count.
 // kForce: the lattice has a body force (the Guo source and the half-force
 // velocity shift); without one those terms are zero and are left out.
-template <int S, bool kForce>
+// kStream: the stores carry the non-temporal hint.
+template <int S, bool kForce, bool kStream>
 __device__ __forceinline__ void collide_store_f(const StepArgs &a, const float (&g)[kQ], bool fluid, uint32_t idx,
                                                 typename Store<S>::T *__restrict__ dst)
 {
     using St = Store<S>;
     const size_t Ns = (size_t)a.Ns;
+    auto put = [](typename St::T *p, float v) {
+        if constexpr (kStream) St::stnt(p, v);
+        else St::st(p, v);
+    };
     // moments in opposite pairs (i, i+9): even and odd parts
     float pe[10], po[10];
 #pragma unroll
@@ -167,7 +172,7 @@ __device__ __forceinline__ void collide_store_f(const StepArgs &a, const float (
     const float a1 = w1 * A, a2 = w2 * A, b1 = w1 * B, b2 = w2 * B, d1 = w1 * D, d2 = w2 * D;
     const float e1 = 9.0f * w1 * cf, e2 = 9.0f * w2 * cf;   // times c.F: the source's cu term
     const float o1 = 3.0f * w1 * cf, o2 = 3.0f * w2 * cf;   // times c.F: the source's odd term
-    St::stnt(at(dst, idx), om1 * g[0] + (float)wgt(0) * A);
+    put(at(dst, idx), om1 * g[0] + (float)wgt(0) * A);
 #pragma unroll
     for (int i = 1; i <= 9; ++i) {
         const bool axis = wgt(i) == wgt(1);
@@ -182,8 +187,8 @@ __device__ __forceinline__ void collide_store_f(const StepArgs &a, const float (
             od = (axis ? d1 : d2) * cu;
         }
         const float vp = om1 * g[i] + (ev + od), vm = om1 * g[i + 9] + (ev - od);
-        St::stnt(at(dst + (size_t)i * Ns, idx), vp);
-        St::stnt(at(dst + (size_t)(i + 9) * Ns, idx), vm);
+        put(at(dst + (size_t)i * Ns, idx), vp);
+        put(at(dst + (size_t)(i + 9) * Ns, idx), vm);
     }
 }
 
@@ -191,10 +196,13 @@ template <int S>
 __device__ __forceinline__ void collide_store(const StepArgs &a, const float (&g)[kQ], bool fluid, uint32_t idx,
                                               typename Store<S>::T *__restrict__ dst)
 {
-    if (a.fx != 0.0f || a.fy != 0.0f || a.fz != 0.0f)
-        collide_store_f<S, true>(a, g, fluid, idx, dst);
-    else
-        collide_store_f<S, false>(a, g, fluid, idx, dst);
+    if (a.fx != 0.0f || a.fy != 0.0f || a.fz != 0.0f) {
+        if (a.stream_out) collide_store_f<S, true, true>(a, g, fluid, idx, dst);
+        else collide_store_f<S, true, false>(a, g, fluid, idx, dst);
+    } else {
+        if (a.stream_out) collide_store_f<S, false, true>(a, g, fluid, idx, dst);
+        else collide_store_f<S, false, false>(a, g, fluid, idx, dst);
+    }
 }
 
 }  // namespace dev

@@ -517,6 +517,7 @@ __device__ __forceinline__ void fused_tile(ArgPtr f, const void *srcv, void *dst
     a.fy = f->s.fy;
     a.fz = f->s.fz;
     a.flag = f->s.flag;
+    a.stream_out = f->s.stream_out;
     a.zieb_state = f->s.zieb_state;
     // index of the lane's node
     const uint32_t idx = (uint32_t)x + (uint32_t)nx * ((uint32_t)y + (uint32_t)ny * (uint32_t)z);
@@ -560,7 +561,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) 
             finish_value(f.fin, i);
     // (f is the kernel's only argument: it lies at the segment's start)
     const ArgPtr p = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
-    fused_tile<S, TX, TY, TZ>(p, f.s.src, f.s.dst, xcd_remap(blockIdx.x, gridDim.x), lds);
+    const int t = xcd_remap<kTileChunk<S>>(blockIdx.x, gridDim.x);
+    fused_tile<S, TX, TY, TZ>(p, f.s.src, f.s.dst, f.s.backward ? (int)gridDim.x - 1 - t : t, lds);
 }
 
 __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs fa)
@@ -598,8 +600,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6, 6))) 
     const void *src = nullptr;
     void *dst = nullptr;
     for (int k = 0;; ++k) {
-        const int gt = xcd_item(xcd, __builtin_amdgcn_readfirstlane(next[k & 1]));
+        int gt = xcd_item<kTileChunk<S>>(xcd, __builtin_amdgcn_readfirstlane(next[k & 1]));
         if (gt >= b.total_tiles) break;  // the XCD's later items lie beyond too
+        if (b.cur[0]) gt = b.total_tiles - 1 - gt;  // every other step, as for one lattice
         // the next tile is taken now, its atomic in flight during this one
         int pre = 0;
         if (threadIdx.x == 0) pre = atomicAdd(q, 1);

@@ -47,6 +47,8 @@ struct StepArgs {
     int Ns;                       // stride between direction arrays (elements, >= N)
     int tile;                     // TileShape
     int ntx, nty, ntz, n_tiles;
+    int backward;                 // take the tiles from the last to the first
+    int stream_out;               // store with the non-temporal hint
     float tau0, smag_k, rho0;     // smag_k = 18 sqrt(2) C^2
     float fx, fy, fz;
     const uint16_t *own;

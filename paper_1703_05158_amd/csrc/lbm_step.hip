@@ -91,7 +91,8 @@ __global__ __launch_bounds__(kBlock) void k_step(StepArgs a)
 {
     if (threadIdx.x < 64)
         for (int w = blockIdx.x; w < a.n_wsum; w += gridDim.x) wall_total(a, w);
-    tile_step<S, TX, TY, TZ>(a, xcd_remap(blockIdx.x, gridDim.x));
+    const int t = xcd_remap<kTileChunk<S>>(blockIdx.x, gridDim.x);
+    tile_step<S, TX, TY, TZ>(a, a.backward ? (int)gridDim.x - 1 - t : t);
 }
 
 template <int S>
