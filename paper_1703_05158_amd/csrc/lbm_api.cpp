@@ -16,7 +16,9 @@
 #include <cstring>
 #include <fstream>
 #include <map>
+#include <mutex>
 #include <new>
+#include <set>
 #include <sstream>
 #include <string>
 #include <utility>
@@ -83,6 +85,11 @@ struct lbm_ctx {
     int n_order = 0;                   // body count the order was made for (0: none)
     int order_age = 0;                 // host body tables staged since the order was made
     hipEvent_t stage_evt = nullptr;
+    // device memory of the drag gradient, kept for the next one (see
+    // gradient_memory); grad_dev: the device it is on
+    char *grad_mem = nullptr;
+    size_t grad_bytes = 0;
+    int grad_dev = 0;
     bool initialized = false;
     int steps_done = 0;
     int64_t device_bytes = 0;
@@ -142,10 +149,46 @@ hipError_t cleared(hipError_t e)
     return e;
 }
 
+// Handles that keep device memory of a finished drag gradient.  When an
+// allocation of the library fails, what they keep on that device is given
+// back and the allocation tried once more.  A handle is in the set only
+// between its calls, when no queued work uses that memory.
+std::mutex kept_mutex;
+std::set<lbm_ctx *> kept;
+
+void give_back(lbm_ctx *h)  // kept_mutex held, or h not in the set
+{
+    if (h->grad_mem) (void)hipFree(h->grad_mem);
+    h->grad_mem = nullptr;
+    h->device_bytes -= (int64_t)h->grad_bytes;
+    h->grad_bytes = 0;
+}
+
+hipError_t device_alloc(void **p, size_t bytes)
+{
+    hipError_t e = cleared(hipMalloc(p, bytes ? bytes : 16));
+    if (e != hipErrorOutOfMemory) return e;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return e;
+    bool freed = false;
+    {
+        std::lock_guard<std::mutex> lock(kept_mutex);
+        for (auto it = kept.begin(); it != kept.end();)
+            if ((*it)->grad_dev == dev) {
+                give_back(*it);
+                it = kept.erase(it);
+                freed = true;
+            } else {
+                ++it;
+            }
+    }
+    return freed ? cleared(hipMalloc(p, bytes ? bytes : 16)) : e;
+}
+
 template <typename T>
 hipError_t dalloc(lbm_ctx *h, T **p, size_t bytes)
 {
-    hipError_t e = cleared(hipMalloc((void **)p, bytes ? bytes : 16));
+    hipError_t e = device_alloc((void **)p, bytes);
     if (e == hipSuccess) h->device_bytes += (int64_t)bytes;
     return e;
 }
@@ -654,6 +697,11 @@ void lbm_destroy(lbm_handle h)
 {
     if (!h) return;
     (void)hipStreamSynchronize(h->stream);
+    {
+        std::lock_guard<std::mutex> lock(kept_mutex);
+        kept.erase(h);
+    }
+    give_back(h);
     for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
     free_wall_links(h);
     void *dev[] = {h->pop[0], h->pop[1], h->own, h->bits, h->lost, h->lrec, h->wall_map, h->tab[0], h->tab[1], h->walls, h->wrec,
@@ -845,7 +893,9 @@ namespace {
 // boundary-link pass and the pull-collide kernel.  With fix, the fused kernel
 // runs whatever the path, its force sums going to fix (bodies first, then the
 // wall copies right after them) instead of the handle's buffers.
-lbm_status step_once(lbm_ctx *h, unsigned long long *fix = nullptr)
+// With src or dst, the step reads or writes that buffer in place of the
+// handle's current or spare one.
+lbm_status step_once(lbm_ctx *h, unsigned long long *fix = nullptr, void *src = nullptr, void *dst = nullptr)
 {
     const lbm_config &c = h->cfg;
     std::array<hipEvent_t, 4> ev{};
@@ -866,6 +916,8 @@ lbm_status step_once(lbm_ctx *h, unsigned long long *fix = nullptr)
         }
         ev[2] = ev[1];
         FusedArgs f = fused_args(h);
+        if (src) f.s.src = src;
+        if (dst) f.s.dst = dst;
         if (fix) {
             f.fsum = fix;
             f.wall_base = h->nb_state;
@@ -882,10 +934,13 @@ lbm_status step_once(lbm_ctx *h, unsigned long long *fix = nullptr)
         if (prof) HIP_TRY(h, prof_mark(h, &ev[1]));
         TRY(finish_forces(h, nullptr));
         LinkArgs la = link_args(h);
+        if (src) la.pop = src;
         HIP_TRY(h, launch_links(c.storage, la, h->stream));
         if (prof) HIP_TRY(h, prof_mark(h, &ev[2]));
         // the step kernel's first workgroups add up the wall chunks
         StepArgs a = step_args(h);
+        if (src) a.src = src;
+        if (dst) a.dst = dst;
         a.n_wsum = la.n_walls;
         a.wsum_nb = la.nb;
         a.wsum_part = h->wl_part;
@@ -1323,6 +1378,37 @@ lbm_status lbm_set_body_force(lbm_handle h, const double *F)
     return LBM_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// The most device memory of a drag gradient that a handle keeps for the next
+// one: 96x96x192 nodes with 200 steps and a checkpoint every 20 take 4.3 GB.
+constexpr size_t kMaxKept = (size_t)8 << 30;
+
+// At least `bytes` of device memory for a drag gradient, the one kept from the
+// last if it is large enough.  Its contents are undefined.  Allocated and
+// freed in each call, 25 buffers of 135 MB cost 7 ms of a 24 ms gradient, and
+// at times the freed memory has to be wiped before it is given out again (up
+// to 70 ms).
+lbm_status gradient_memory(lbm_ctx *h, size_t bytes, int nck, int nseg)
+{
+    if (bytes <= h->grad_bytes) return LBM_OK;
+    give_back(h);
+    void *p = nullptr;
+    if (device_alloc(&p, bytes) != hipSuccess)
+        return fail(h, LBM_ERR_OOM, "no device memory for %d checkpoints and %d recomputed states", nck, nseg);
+    h->grad_mem = static_cast<char *>(p);
+    h->grad_bytes = bytes;
+    h->device_bytes += (int64_t)bytes;
+    HIP_TRY(h, hipGetDevice(&h->grad_dev));
+    return LBM_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
 lbm_status lbm_drag_gradient(lbm_handle h, int32_t nsteps, int32_t ckpt, double *J, double *dJdF, double *dJdV)
 {
     if (!h) return LBM_ERR_ARG;
@@ -1337,111 +1423,134 @@ lbm_status lbm_drag_gradient(lbm_handle h, int32_t nsteps, int32_t ckpt, double 
     const size_t popb = sizeof(float) * kQ * (size_t)h->Ns;
     const int nck = (nsteps + ckpt - 1) / ckpt;
     const int nseg = std::min(ckpt, nsteps);
-    // device buffers of this call
-    std::vector<void *> bufs;
-    bool oom = false;
-    auto get = [&](size_t bytes) -> void * {
-        void *p = nullptr;
-        if (cleared(hipMalloc(&p, bytes ? bytes : 16)) != hipSuccess) {
-            oom = true;
-            return nullptr;
-        }
-        bufs.push_back(p);
-        return p;
-    };
-    auto release = [&]() {
-        (void)hipStreamSynchronize(h->stream);
-        for (void *p : bufs) (void)hipFree(p);
-        bufs.clear();
-    };
-    // every return (an error of a HIP call included) frees the buffers and
-    // leaves profiling as it was
-    const bool prof = h->prof;
+    // every return (an error of a HIP call included) waits for the queued work,
+    // keeps or frees the device memory and leaves profiling as it was
     struct Exit {
-        decltype(release) &free_all;
         lbm_ctx *h;
         bool prof;
         ~Exit()
         {
-            free_all();
+            (void)hipStreamSynchronize(h->stream);
             h->prof = prof;
+            if (h->grad_bytes > kMaxKept) give_back(h);
+            std::lock_guard<std::mutex> lock(kept_mutex);
+            if (h->grad_mem) kept.insert(h);
         }
-    } on_exit{release, h, prof};
+    } on_exit{h, h->prof};
+    {
+        std::lock_guard<std::mutex> lock(kept_mutex);
+        kept.erase(h);
+    }
+    const bool prof = h->prof;
+    // the spheres are fixed: their links are counted and listed once, each
+    // sphere's padded to whole wavefronts
+    LinkArgs lg = link_args(h);
+    std::vector<int> cnt((size_t)std::max(nb, 1), 0), first(cnt);
+    auto pad = [](size_t v) { return (v + 255) / 256 * 256; };
+    const size_t firsts = pad(sizeof(int) * cnt.size());
+    TRY(gradient_memory(h, firsts, nck, nseg));
+    if (nb > 0) {
+        int *d_first = reinterpret_cast<int *>(h->grad_mem);
+        HIP_TRY(h, launch_count_links(lg, d_first, h->stream));
+        TRY(copy_sync(h, cnt.data(), d_first, sizeof(int) * (size_t)nb, hipMemcpyDeviceToHost));
+    }
+    SphereLinks links{};
+    std::vector<uint32_t> sphere;
+    for (int b = 0; b < nb; ++b) {
+        first[(size_t)b] = links.n;
+        const int waves = (cnt[(size_t)b] + 63) / 64;
+        links.n += 64 * waves;
+        sphere.insert(sphere.end(), (size_t)waves, (uint32_t)b);
+    }
+    const size_t list = sizeof(uint32_t) * (size_t)links.n, sums = sizeof(double) * 3 * (size_t)h->n_tiles;
+    const size_t dVb = sizeof(double) * 3 * (size_t)std::max(nb, 1);
+    TRY(gradient_memory(h, firsts + (size_t)(nck + nseg - 1 + 2) * popb + 6 * pad(list) +
+                               pad(sizeof(uint32_t) * sphere.size()) + pad(sums) + pad(sizeof(double) * 3) + pad(dVb),
+                        nck, nseg));
+    int *d_first = reinterpret_cast<int *>(h->grad_mem);
+    char *mem = h->grad_mem + firsts;
+    auto take = [&](size_t bytes) {
+        char *p = mem;
+        mem += pad(bytes);
+        return p;
+    };
+    // state k of a segment: its checkpoint (k = 0), else seg[k]
     std::vector<float *> ck((size_t)nck), seg((size_t)nseg);
-    for (auto &b : ck) b = static_cast<float *>(get(popb));
-    for (auto &b : seg) b = static_cast<float *>(get(popb));
-    float *lam[2] = {static_cast<float *>(get(popb)), static_cast<float *>(get(popb))};
-    const int nbt = std::max(nb + h->n_walls, 1);
-    double *fscratch = static_cast<double *>(get(sizeof(double) * 6 * (size_t)nbt));
-    double *accsave = static_cast<double *>(get(sizeof(double) * 6 * (size_t)nbt));
-    double *dF_tile = static_cast<double *>(get(sizeof(double) * 3 * (size_t)h->n_tiles));
-    double *dF = static_cast<double *>(get(sizeof(double) * 3));
-    double *dV = static_cast<double *>(get(sizeof(double) * 3 * (size_t)std::max(nb, 1)));
-    if (oom) return fail(h, LBM_ERR_OOM, "no device memory for %d checkpoints and %d recomputed states", nck, nseg);
+    for (auto &b : ck) b = reinterpret_cast<float *>(take(popb));
+    for (int k = 1; k < nseg; ++k) seg[(size_t)k] = reinterpret_cast<float *>(take(popb));
+    float *mu[2] = {reinterpret_cast<float *>(take(popb)), reinterpret_cast<float *>(take(popb))};
+    for (uint32_t **p : {&links.x, &links.p, &links.b, &links.code}) *p = reinterpret_cast<uint32_t *>(take(list));
+    for (float **p : {&links.q, &links.mw}) *p = reinterpret_cast<float *>(take(list));
+    links.sphere = reinterpret_cast<uint32_t *>(take(sizeof(uint32_t) * sphere.size()));
+    double *dF_tile = reinterpret_cast<double *>(take(sums));
+    double *dF = reinterpret_cast<double *>(take(sizeof(double) * 3));
+    double *dV = reinterpret_cast<double *>(take(dVb));
+    if (links.n > 0) {
+        HIP_TRY(h, hipMemsetAsync(links.code, 0, list, h->stream));
+        TRY(copy_sync(h, d_first, first.data(), sizeof(int) * (size_t)nb, hipMemcpyHostToDevice));
+        TRY(copy_sync(h, links.sphere, sphere.data(), sizeof(uint32_t) * sphere.size(), hipMemcpyHostToDevice));
+        HIP_TRY(h, launch_fill_links(lg, links, d_first, h->stream));
+    }
     const lbm_config &c = h->cfg;
     // forward, keeping every ckpt-th state: the steps of lbm_step, so that the
-    // state and forces left behind are those of plain stepping
+    // state and forces left behind are those of plain stepping.  The last
+    // segment's steps write their states where the reverse sweep takes them
+    // from.
     h->prof = false;
+    const int last = (nck - 1) * ckpt;
     for (int n = 0; n < nsteps; ++n) {
-        if (n % ckpt == 0) HIP_TRY(h, hipMemcpyAsync(ck[(size_t)(n / ckpt)], h->pop[h->cur], popb, hipMemcpyDeviceToDevice, h->stream));
-        const lbm_status sst = step_once(h);
-        if (sst != LBM_OK) return sst;
+        if (n % ckpt == 0)
+            HIP_TRY(h, hipMemcpyAsync(ck[(size_t)(n / ckpt)], h->pop[h->cur], popb, hipMemcpyDeviceToDevice, h->stream));
+        void *src = n > last ? seg[(size_t)(n - last)] : nullptr;
+        void *dst = n >= last && n + 1 < nsteps ? seg[(size_t)(n + 1 - last)] : nullptr;
+        TRY(step_once(h, nullptr, src, dst));
     }
     h->prof = prof;
     TRY(finish_forces(h, nullptr));
+    const int nbt = std::max(nb + h->n_walls, 1);
     std::vector<double> acc_h((size_t)6 * nbt);
     TRY(copy_sync(h, acc_h.data(), h->acc, sizeof(double) * 6 * nbt, hipMemcpyDeviceToHost));
     double Jv = 0.0;
     for (int b = 0; b < nb; ++b) Jv += acc_h[(size_t)6 * b];
-    HIP_TRY(h, hipMemcpyAsync(accsave, h->acc, sizeof(double) * 6 * nbt, hipMemcpyDeviceToDevice, h->stream));
     // backward: the objective's derivative gives the adjoint of P_{N-1}
-    HIP_TRY(h, hipMemsetAsync(dF_tile, 0, sizeof(double) * 3 * h->n_tiles, h->stream));
-    HIP_TRY(h, hipMemsetAsync(dV, 0, sizeof(double) * 3 * std::max(nb, 1), h->stream));
-    HIP_TRY(h, hipMemsetAsync(lam[0], 0, popb, h->stream));
-    LinkArgs lg = link_args(h);
-    lg.out = fscratch;
-    AdjLinkArgs al{lg, nullptr, lam[0], dV};
-    HIP_TRY(h, launch_adj_links(al, h->stream));
-    int li = 0;  // lam[li] is the adjoint of P_m
+    HIP_TRY(h, hipMemsetAsync(dF_tile, 0, sums, h->stream));
+    HIP_TRY(h, hipMemsetAsync(dV, 0, dVb, h->stream));
+    HIP_TRY(h, hipMemsetAsync(mu[0], 0, popb, h->stream));
+    AdjLinkArgs al{links, h->Ns, (float)c.rho0, mu[0], dV};
+    HIP_TRY(h, launch_adj_links(al, true, h->stream));
+    int li = 0;  // mu[li] belongs to the step after the next reverse one
     for (int s = nck - 1; s >= 0; --s) {
         const int start = s * ckpt, end = std::min(start + ckpt, nsteps);
-        // recompute P_start .. P_{end-1} of the segment
-        HIP_TRY(h, hipMemcpyAsync(seg[0], ck[(size_t)s], popb, hipMemcpyDeviceToDevice, h->stream));
-        for (int k = start + 1; k < end; ++k) {
-            LinkArgs la = link_args(h);
-            la.pop = seg[(size_t)(k - 1 - start)];
-            la.out = fscratch;
-            HIP_TRY(h, launch_links(c.storage, la, h->stream));
-            StepArgs a = step_args(h);
-            a.flag = nullptr;
-            a.src = seg[(size_t)(k - 1 - start)];
-            a.dst = seg[(size_t)(k - start)];
-            HIP_TRY(h, launch_step(c.storage, a, h->stream));
-        }
+        auto state = [&](int k) { return k == start ? ck[(size_t)s] : seg[(size_t)(k - start)]; };
+        // recompute P_{start+1} .. P_{end-1}, each state with its link values
+        // in the solid slots (the last segment's states are there already,
+        // without them)
+        int linked = start;  // states below have them
+        if (s < nck - 1)
+            for (; linked + 1 < end; ++linked) {
+                HIP_TRY(h, launch_listed_links(links, state(linked), h->Ns, h->stream));
+                StepArgs a = step_args(h);
+                a.flag = nullptr;
+                a.src = state(linked);
+                a.dst = state(linked + 1);
+                a.backward = linked & 1;
+                HIP_TRY(h, launch_step(c.storage, a, h->stream));
+            }
         // steps m = k + 1 whose source P_k lies in the segment, m from N - 1 down
         for (int m = std::min(end, nsteps - 1); m >= start + 1; --m) {
-            float *src = seg[(size_t)(m - 1 - start)];
-            if (m == end) {
-                // the recompute stopped before step end: put its link values
-                // into the solid slots of P_{end-1}; for earlier steps the
-                // recompute's own link pass left them there
-                LinkArgs la = link_args(h);
-                la.pop = src;
-                la.out = fscratch;
-                HIP_TRY(h, launch_links(c.storage, la, h->stream));
-            }
+            if (m - 1 >= linked) HIP_TRY(h, launch_listed_links(links, state(m - 1), h->Ns, h->stream));
             StepArgs a = step_args(h);
             a.flag = nullptr;
-            a.src = src;
-            AdjStepArgs ga{a, lam[li], lam[1 - li], dF_tile};
+            a.src = state(m - 1);
+            a.backward = m & 1;
+            AdjStepArgs ga{a, mu[li], mu[1 - li], dF_tile};
             HIP_TRY(h, launch_adj_collide(ga, h->stream));
-            AdjLinkArgs am{lg, lam[1 - li], lam[1 - li], dV};
-            HIP_TRY(h, launch_adj_links(am, h->stream));
+            al.mu = mu[1 - li];
+            HIP_TRY(h, launch_adj_links(al, false, h->stream));
             li = 1 - li;
         }
     }
     HIP_TRY(h, launch_adj_reduce(dF_tile, h->n_tiles, dF, h->stream));
-    HIP_TRY(h, hipMemcpyAsync(h->acc, accsave, sizeof(double) * 6 * nbt, hipMemcpyDeviceToDevice, h->stream));
     TRY(copy_sync(h, dJdF, dF, sizeof(double) * 3, hipMemcpyDeviceToHost));
     if (nb > 0) TRY(copy_sync(h, dJdV, dV, sizeof(double) * 3 * nb, hipMemcpyDeviceToHost));
     *J = Jv;

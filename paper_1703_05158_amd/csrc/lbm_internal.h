@@ -173,16 +173,26 @@ struct BatchStepArgs {
 // storage, fixed spheres, no walls).
 struct AdjStepArgs {
     StepArgs a;                   // src = the state P_{n-1} the step starts from
-    const float *lam;             // adjoint of the post-collision state P_n, [19][Ns]
-    float *lam_prev;              // adjoint of P_{n-1}, [19][Ns]: every entry is written (see k_adj_collide)
+    const float *mu_in;           // adjoint of the streamed populations of the step after, [19][Ns]
+    float *mu;                    // the same of this step: every entry of a wavefront with fluid is written
     double *dF_tile;              // [n_tiles][3], accumulated over the steps
 };
 
+// The links of fixed spheres, listed once for a gradient: padded per sphere to
+// whole wavefronts of 64.
+struct SphereLinks {
+    uint32_t *x, *p, *b;          // the fluid node, the solid node x + c_K, the node behind x + c_I
+    uint32_t *code;               // I | (node behind fluid) << 5 | 1 << 6 | (second to its shared slot) << 7; 0: padding
+    float *q, *mw;                // link fraction and moving-boundary term, as the step forms them
+    uint32_t *sphere;             // [n / 64]: the wavefront's sphere
+    int n;                        // padded length
+};
+
 struct AdjLinkArgs {
-    LinkArgs a;                   // geometry and bodies; pop unused
-    const float *mu;              // adjoint of f_n at the links, in the solid slots (p, I) of a
-                                  // [19][Ns] array; null: the objective's own derivative
-    float *lam;                   // adjoint of P_{n-1}, links add into it
+    SphereLinks l;
+    int Ns;
+    float rho0;
+    float *mu;                    // adjoint of the streamed populations, [19][Ns]
     double *dV;                   // [nb][3], accumulated over the steps
 };
 
@@ -230,7 +240,14 @@ hipError_t launch_batch_flip(int *cur, int n, int *queue, hipStream_t s);
 
 hipError_t launch_zieb_update(int storage, const ZiebArgs &z, hipStream_t s);
 hipError_t launch_adj_collide(const AdjStepArgs &g, hipStream_t s);
-hipError_t launch_adj_links(const AdjLinkArgs &g, hipStream_t s);
+// Links per sphere (cnt, cleared by the caller's size: one int per sphere).
+hipError_t launch_count_links(const LinkArgs &a, int *cnt, hipStream_t s);
+// The links of sphere b from entry first[b] on; padding is left alone.
+hipError_t launch_fill_links(const LinkArgs &a, const SphereLinks &l, const int *first, hipStream_t s);
+// The link values of state pop into the solid slots, from the list.
+hipError_t launch_listed_links(const SphereLinks &l, float *pop, int Ns, hipStream_t s);
+// The links' part of a reverse step (objective: of J itself).
+hipError_t launch_adj_links(const AdjLinkArgs &g, bool objective, hipStream_t s);
 hipError_t launch_adj_reduce(const double *dF_tile, int n_tiles, double *dF, hipStream_t s);
 
 hipError_t launch_walls_init(const uint8_t *wall, uint16_t *own, int N, hipStream_t s);

@@ -184,16 +184,18 @@ __global__ __launch_bounds__(kBlock) void k_zieb_update(ZiebArgs z)
 // For a step P_n = C(f_n), f_n = S(P_{n-1}), k_adj_collide turns the adjoint
 // lambda_n of P_n into the adjoint mu_n of the streamed populations f_n,
 // mu = (dC/df)^T lambda, node by node, and adds lambda . dC/dF (the body
-// force) to per-tile sums.  It applies the transpose of plain streaming in
-// the same pass: f_n(x)[i] came from P_{n-1}(x - c_i)[i], so mu(x)[i] is
-// pushed to lambda_{n-1}(x - c_i)[i].  Streaming is a permutation, so every
-// entry of lambda_{n-1} is written once: solid nodes push zeros (nothing was
-// pulled from them), and where x - c_i is solid the pushed value is the
-// adjoint of a link value, which the link kernel then takes from that solid
-// slot and adds to the populations the link was formed from.  The collision is recomputed from f_n:
+// force) to per-tile sums.  mu_n(x)[i] is stored at x, in whole lines; the
+// transpose of streaming is in the loads: f_{n+1}(x + c_i)[i] came from
+// P_n(x)[i], so lambda_n(x)[i] is pulled from mu_{n+1}(x + c_i)[i].  Where x +
+// c_i is solid, that slot holds what the link (x, i) hands back, put there by
+// the link kernel, which also adds the links' parts for the populations they
+// were formed from besides.  The collision is recomputed from f_n:
 // moments, the equilibrium, Pi, Q = Pi:Pi, tau* and the Guo source, as in
 // the forward step (Sec. 2.2); the derivative of sqrt(Q) is taken as
 // 1/(2 sqrt(Q + 1e-30)), finite where Q = 0.
+// What bounds it: HBM (403 MB on the 96x96x192 box in 92 us) with some 1500
+// vector instructions per wavefront close behind; pushing mu to x - c_i, in
+// lines that two wavefronts share, it took 100 us.
 
 // mu = (dC/df)^T lam at one node (deviations g = f - w rho0), and the body-
 // force part added to Fb.
@@ -208,7 +210,7 @@ __device__ __forceinline__ void collide_adjoint(const StepArgs &a, const float (
         rd += g[i];
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
-            j[p] += c[p] * g[i];
+            if (c[p]) j[p] += c[p] * g[i];
 #pragma unroll
             for (int q = 0; q < 3; ++q)
                 if (c[p] * c[q]) S[p][q] += c[p] * c[q] * g[i];
@@ -237,7 +239,7 @@ __device__ __forceinline__ void collide_adjoint(const StepArgs &a, const float (
     for (int i = 0; i < kQ; ++i) {
         const float w = (float)wgt(i);
         const float cu = CX[i] * u[0] + CY[i] * u[1] + CZ[i] * u[2];
-        const float cF = CX[i] * F[0] + CY[i] * F[1] + CZ[i] * F[2];
+        const float cF = cdot(CX[i], CY[i], CZ[i], F[0], F[1], F[2]);
         const float geq = w * (rd + rho * (3.0f * cu + 4.5f * cu * cu - 1.5f * uu));
         const float src = w * (3.0f * (cF - uF) + 9.0f * cu * cF);
         Ob += lam[i] * (-(g[i] - geq) - 0.5f * src);
@@ -260,14 +262,17 @@ __device__ __forceinline__ void collide_adjoint(const StepArgs &a, const float (
         const int c[3] = {CX[i], CY[i], CZ[i]};
         const float w = (float)wgt(i);
         const float cu = c[0] * u[0] + c[1] * u[1] + c[2] * u[2];
-        const float cF = c[0] * F[0] + c[1] * F[1] + c[2] * F[2];
+        const float cF = cdot(c[0], c[1], c[2], F[0], F[1], F[2]);
         const float gq = om * lam[i] * w;   // adjoint of geq_i, times w_i
         const float sq = cs * lam[i] * w;   // adjoint of the source S_i, times w_i
         rdb += gq;
         rhob += gq * (3.0f * cu + 4.5f * cu * cu - 1.5f * uu);
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
-            ub[p] += gq * rho * (3.0f * c[p] + 9.0f * cu * c[p] - 3.0f * u[p]) + sq * (-3.0f * F[p] + 9.0f * c[p] * cF);
+            if (c[p])
+                ub[p] += gq * rho * (3.0f * c[p] + 9.0f * cu * c[p] - 3.0f * u[p]) + sq * (-3.0f * F[p] + 9.0f * c[p] * cF);
+            else
+                ub[p] += gq * rho * (-3.0f * u[p]) + sq * (-3.0f * F[p]);
             fb[p] += (double)(sq * (3.0f * (c[p] - u[p]) + 9.0f * cu * c[p]));
         }
     }
@@ -289,7 +294,10 @@ __device__ __forceinline__ void collide_adjoint(const StepArgs &a, const float (
 #pragma unroll
     for (int i = 0; i < kQ; ++i) {
         const int c[3] = {CX[i], CY[i], CZ[i]};
-        float m = (1.0f - om) * lam[i] + rdb + jb[0] * c[0] + jb[1] * c[1] + jb[2] * c[2];
+        float m = (1.0f - om) * lam[i] + rdb;
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            if (c[p]) m += jb[p] * c[p];
 #pragma unroll
         for (int p = 0; p < 3; ++p)
 #pragma unroll
@@ -307,7 +315,8 @@ __global__ __launch_bounds__(kBlock) void k_adj_collide(AdjStepArgs ga)
     const size_t Ns = (size_t)a.Ns;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const int tid = threadIdx.x;
-    const int t = xcd_remap(blockIdx.x, gridDim.x);
+    int t = xcd_remap<kTileChunk<0>>(blockIdx.x, gridDim.x);
+    if (a.backward) t = (int)gridDim.x - 1 - t;
     const int r = t / a.ntx;
     const int x = (t - r * a.ntx) * TX + tid % TX;
     const int y = (r % a.nty) * TY + (tid / TX) % TY;
@@ -316,38 +325,29 @@ __global__ __launch_bounds__(kBlock) void k_adj_collide(AdjStepArgs ga)
     const uint32_t idx = in ? (uint32_t)(x + nx * (y + ny * z)) : 0u;
     const bool fluid = in && *at(a.own, idx) >= kVacated;
     double Fb[3] = {0.0, 0.0, 0.0};
-    if (fluid) {
+    if (__ballot(fluid)) {
         float g[kQ], lam[kQ], mu[kQ];
-        const int xp = x + 1 == nx ? 0 : x + 1, xm = x == 0 ? nx - 1 : x - 1;
-        const int yp = y + 1 == ny ? 0 : y + 1, ym = y == 0 ? ny - 1 : y - 1;
-        const int zp = z + 1 == nz ? 0 : z + 1, zm = z == 0 ? nz - 1 : z - 1;
+        if (fluid) {
+            // index offsets to the neighbours at -1, 0, +1 along each axis
+            const uint32_t ox[3] = {(uint32_t)(x == 0 ? nx - 1 : x - 1), (uint32_t)x, (uint32_t)(x + 1 == nx ? 0 : x + 1)};
+            const uint32_t oy[3] = {(uint32_t)nx * (uint32_t)(y == 0 ? ny - 1 : y - 1), (uint32_t)nx * (uint32_t)y,
+                                    (uint32_t)nx * (uint32_t)(y + 1 == ny ? 0 : y + 1)};
+            const uint32_t nxy = (uint32_t)nx * (uint32_t)ny;
+            const uint32_t oz[3] = {nxy * (uint32_t)(z == 0 ? nz - 1 : z - 1), nxy * (uint32_t)z,
+                                    nxy * (uint32_t)(z + 1 == nz ? 0 : z + 1)};
 #pragma unroll
-        for (int i = 0; i < kQ; ++i) {
-            const int sx = CX[i] > 0 ? xm : (CX[i] < 0 ? xp : x);
-            const int sy = CY[i] > 0 ? ym : (CY[i] < 0 ? yp : y);
-            const int sz = CZ[i] > 0 ? zm : (CZ[i] < 0 ? zp : z);
-            g[i] = *at(src + (size_t)i * Ns, (uint32_t)(sx + nx * (sy + ny * sz)));
-            lam[i] = *at(ga.lam + (size_t)i * Ns, idx);
-        }
-        collide_adjoint(a, g, lam, mu, Fb);
+            for (int i = 0; i < kQ; ++i) {
+                g[i] = *at(src + (size_t)i * Ns, ox[1 - CX[i]] + (oy[1 - CY[i]] + oz[1 - CZ[i]]));
+                lam[i] = *at(ga.mu_in + (size_t)i * Ns, ox[1 + CX[i]] + (oy[1 + CY[i]] + oz[1 + CZ[i]]));
+            }
+            collide_adjoint(a, g, lam, mu, Fb);
+        } else {
 #pragma unroll
-        for (int i = 0; i < kQ; ++i) {
-            const int sx = CX[i] > 0 ? xm : (CX[i] < 0 ? xp : x);
-            const int sy = CY[i] > 0 ? ym : (CY[i] < 0 ? yp : y);
-            const int sz = CZ[i] > 0 ? zm : (CZ[i] < 0 ? zp : z);
-            *at(ga.lam_prev + (size_t)i * Ns, (uint32_t)(sx + nx * (sy + ny * sz))) = mu[i];
+            for (int i = 0; i < kQ; ++i) mu[i] = 0.0f;
         }
-    } else if (in) {
-        const int xp = x + 1 == nx ? 0 : x + 1, xm = x == 0 ? nx - 1 : x - 1;
-        const int yp = y + 1 == ny ? 0 : y + 1, ym = y == 0 ? ny - 1 : y - 1;
-        const int zp = z + 1 == nz ? 0 : z + 1, zm = z == 0 ? nz - 1 : z - 1;
+        if (in)  // whole wavefronts store, solid lanes zeros (no partial lines)
 #pragma unroll
-        for (int i = 0; i < kQ; ++i) {
-            const int sx = CX[i] > 0 ? xm : (CX[i] < 0 ? xp : x);
-            const int sy = CY[i] > 0 ? ym : (CY[i] < 0 ? yp : y);
-            const int sz = CZ[i] > 0 ? zm : (CZ[i] < 0 ? zp : z);
-            *at(ga.lam_prev + (size_t)i * Ns, (uint32_t)(sx + nx * (sy + ny * sz))) = 0.0f;
-        }
+            for (int i = 0; i < kQ; ++i) *at(ga.mu + (size_t)i * Ns, idx) = mu[i];
     }
     // body-force part: per-tile sums in a fixed order
     __shared__ double s_red[kBlock / 64][3];
