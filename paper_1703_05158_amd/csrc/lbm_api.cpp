@@ -647,8 +647,15 @@ lbm_status lbm_create(const lbm_config *cfg, lbm_handle *out)
     };
     const size_t popb = (size_t)kQ * h->Ns * h->sbytes;
     const int nbt = c.max_bodies + c.max_walls;
-    // tile shape: 64 nodes along x unless x is a multiple of 32 but not of 64
-    set_tile_shape(h, (c.nx % 64 != 0 && (c.nx % 32 == 0 || c.nx < 32)) ? kTile32x4x2 : kTile64x2x2);
+    // tile shape: 64 nodes along x, unless x is a multiple of 32 but not of 64
+    // (half of the last tile would be empty) and there are tiles enough to
+    // fill the GPU twice; below that a step is one workgroup's chain, which is
+    // shorter where it holds fewer nodes.  Kernel times 64x2x2 / 32x4x2 /
+    // 32x2x4: 24x20x28 7.0 / 7.2 / 7.2 us, 32^3 7.4 / 8.4 / 8.4, 96^3 30.3 / 29.2
+    // / 28.9, 96x96x192 48.9 / 48.9 / 48.3, 96x96x256 81 / 71 / 66, 160x128x128
+    // FP16 70 / 64 / 63.
+    set_tile_shape(h, kTile64x2x2);
+    if (c.nx % 64 != 0 && c.nx % 32 == 0 && h->n_tiles > 512) set_tile_shape(h, kTile32x2x4);
     if (dalloc(h, &h->pop[0], popb) != hipSuccess || dalloc(h, &h->pop[1], popb) != hipSuccess ||
         dalloc(h, &h->own, sizeof(uint16_t) * N + 4) != hipSuccess ||
         dalloc(h, &h->bits, sizeof(uint32_t) * (bit_row_words(c.nx) * ((size_t)c.ny * (size_t)c.nz) + kBitPad)) !=
