@@ -78,7 +78,14 @@ struct lbm_ctx {
     int *flag = nullptr;
     int *flag_host = nullptr;
     double *scratch = nullptr;         // 4N doubles, export/import staging (lazy)
-    double *pinned = nullptr;          // max_bodies * 10 doubles, set_bodies staging
+    // set_bodies staging, two halves of max_bodies * 10 doubles in turn, which a
+    // kernel reads in place; seen[k] (pinned too) becomes ticket[k] when half k
+    // has been read
+    double *pinned = nullptr;
+    unsigned *seen = nullptr;
+    unsigned ticket[2] = {0, 0};
+    int half = 0;                      // the half of the next table
+    unsigned *left = nullptr;          // device counter of k_take_table
     double *forces_pin = nullptr;      // (max_bodies + max_walls) * 6 doubles, get_forces staging
     int *order = nullptr;              // max_bodies: sphere order of the link pass (Morton order of the centres)
     int *order_pin = nullptr;          // its host staging
@@ -673,14 +680,16 @@ lbm_status lbm_create(const lbm_config *cfg, lbm_handle *out)
         dalloc(h, &h->order, sizeof(int) * std::max(c.max_bodies, 1)) != hipSuccess ||
         dalloc(h, &h->zstate, sizeof(ZiebState)) != hipSuccess ||
         dalloc(h, &h->zpart, sizeof(double) * (3 * kZiebMaxBlocks + 1)) != hipSuccess ||
-        dalloc(h, &h->flag, sizeof(int)) != hipSuccess)
+        dalloc(h, &h->left, sizeof(unsigned)) != hipSuccess || dalloc(h, &h->flag, sizeof(int)) != hipSuccess)
         return bail(LBM_ERR_OOM);
-    if (cleared(hipHostMalloc((void **)&h->pinned, sizeof(double) * kBodyStride * std::max(c.max_bodies, 1))) !=
+    if (cleared(hipHostMalloc((void **)&h->pinned, 2 * sizeof(double) * kBodyStride * std::max(c.max_bodies, 1))) !=
             hipSuccess ||
+        cleared(hipHostMalloc((void **)&h->seen, 2 * sizeof(unsigned))) != hipSuccess ||
         cleared(hipHostMalloc((void **)&h->forces_pin, sizeof(double) * 6 * std::max(nbt, 1))) != hipSuccess ||
         cleared(hipHostMalloc((void **)&h->order_pin, sizeof(int) * std::max(c.max_bodies, 1))) != hipSuccess ||
         cleared(hipHostMalloc((void **)&h->flag_host, sizeof(int))) != hipSuccess)
         return bail(LBM_ERR_OOM);
+    h->seen[0] = h->seen[1] = 0;
     if (hipEventCreateWithFlags(&h->stage_evt, hipEventDisableTiming) != hipSuccess) return bail(LBM_ERR_HIP);
     if (hipMemsetAsync(h->wall_map, 0, (size_t)N, h->stream) != hipSuccess ||
         hipMemsetAsync(h->lost, 0, sizeof(int) * 3 * (size_t)std::max(c.max_bodies, 1), h->stream) != hipSuccess ||
@@ -692,6 +701,7 @@ lbm_status lbm_create(const lbm_config *cfg, lbm_handle *out)
         hipMemsetAsync(h->fsum[1], 0, sizeof(unsigned long long) * std::max(fsum_entries(c), (size_t)1), h->stream) !=
             hipSuccess ||
         hipMemsetAsync(h->flag, 0, sizeof(int), h->stream) != hipSuccess ||
+        hipMemsetAsync(h->left, 0, sizeof(unsigned), h->stream) != hipSuccess ||
         hipMemsetAsync(h->zpart + 3 * kZiebMaxBlocks, 0, sizeof(double), h->stream) != hipSuccess)
         return bail(LBM_ERR_HIP);
     if (rasterize_full(h) != LBM_OK) return bail(LBM_ERR_HIP);
@@ -712,10 +722,11 @@ void lbm_destroy(lbm_handle h)
     for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
     free_wall_links(h);
     void *dev[] = {h->pop[0], h->pop[1], h->own, h->bits, h->lost, h->lrec, h->wall_map, h->tab[0], h->tab[1], h->walls, h->wrec,
-                   h->acc, h->fsum[0], h->fsum[1], h->order, h->flag, h->scratch, h->zstate, h->zpart};
+                   h->acc, h->fsum[0], h->fsum[1], h->order, h->left, h->flag, h->scratch, h->zstate, h->zpart};
     for (void *p : dev)
         if (p) (void)hipFree(p);
     if (h->pinned) (void)hipHostFree(h->pinned);
+    if (h->seen) (void)hipHostFree(h->seen);
     if (h->forces_pin) (void)hipHostFree(h->forces_pin);
     if (h->order_pin) (void)hipHostFree(h->order_pin);
     if (h->flag_host) (void)hipHostFree(h->flag_host);
@@ -780,29 +791,24 @@ static uint64_t morton_key(const double *X)
            spread3((uint64_t)(X[2] / 8.0)) << 2;
 }
 
-static lbm_status stage_bodies(lbm_ctx *h, int32_t n)
+// The sphere order of the split path's link pass (the Morton order of the
+// centres in `table`), so that the workgroups on one XCD work on neighbouring
+// spheres, which share population lines.  The order changes no result, and
+// spheres move little between calls: it is made again when the count changes,
+// else every 32nd call.
+static lbm_status refresh_order(lbm_ctx *h, const double *table, int32_t n)
 {
-    // the link pass takes the spheres in Morton order of their centres, so
-    // that the workgroups on one XCD work on neighbouring spheres, which
-    // share population lines.  The order changes no result, and spheres move
-    // little between calls: it is made again when the count changes, else
-    // every 32nd call.
-    HIP_TRY(h, hipMemcpyAsync(h->tab[1 - h->ts], h->pinned, sizeof(double) * kBodyStride * (size_t)n,
-                              hipMemcpyHostToDevice, h->stream));
-    if (n != h->n_order || ++h->order_age >= 32) {
-        std::vector<std::pair<uint64_t, int>> keys((size_t)n);
-        for (int b = 0; b < n; ++b) keys[(size_t)b] = {morton_key(h->pinned + (size_t)b * kBodyStride), b};
-        std::sort(keys.begin(), keys.end());
-        for (int b = 0; b < n; ++b) h->order_pin[b] = keys[(size_t)b].second;
-        if (n > 0)
-            HIP_TRY(h, hipMemcpyAsync(h->order, h->order_pin, sizeof(int) * (size_t)n, hipMemcpyHostToDevice,
-                                      h->stream));
-        h->n_order = n;
-        h->order_age = 0;
-    }
+    if (n == h->n_order && ++h->order_age < 32) return LBM_OK;
+    std::vector<std::pair<uint64_t, int>> keys((size_t)n);
+    for (int b = 0; b < n; ++b) keys[(size_t)b] = {morton_key(table + (size_t)b * kBodyStride), b};
+    std::sort(keys.begin(), keys.end());
+    HIP_TRY(h, hipEventSynchronize(h->stage_evt));  // the last order has been copied
+    for (int b = 0; b < n; ++b) h->order_pin[b] = keys[(size_t)b].second;
+    if (n > 0)
+        HIP_TRY(h, hipMemcpyAsync(h->order, h->order_pin, sizeof(int) * (size_t)n, hipMemcpyHostToDevice, h->stream));
     HIP_TRY(h, hipEventRecord(h->stage_evt, h->stream));
-    h->nb_next = n;
-    h->dirty = true;
+    h->n_order = n;
+    h->order_age = 0;
     return LBM_OK;
 }
 
@@ -825,9 +831,15 @@ lbm_status lbm_set_bodies(lbm_handle h, int32_t n, const double *X, const double
         if (!(R[b] > 0.0 && R[b] < rmax))
             return fail(h, LBM_ERR_ARG, "sphere %d radius %g outside (0, %g)", b, R[b], rmax);
     }
-    HIP_TRY(h, hipEventSynchronize(h->stage_evt));  // staging buffer free again
+    // this half of the staging buffer is free once its last table has been
+    // read; a short look at the word that says so, else the stream
+    const int k = h->half;
+    double *const stage = h->pinned + (size_t)k * kBodyStride * std::max(h->cfg.max_bodies, 1);
+    bool read = false;
+    for (int spin = 0; spin < 2000 && !read; ++spin) read = __atomic_load_n(h->seen + k, __ATOMIC_ACQUIRE) == h->ticket[k];
+    if (!read) HIP_TRY(h, hipStreamSynchronize(h->stream));
     for (int b = 0; b < n; ++b) {
-        double *t = h->pinned + (size_t)b * kBodyStride;
+        double *t = stage + (size_t)b * kBodyStride;
         for (int a = 0; a < 3; ++a) {
             t[a] = X[3 * b + a];
             t[3 + a] = V[3 * b + a];
@@ -835,7 +847,15 @@ lbm_status lbm_set_bodies(lbm_handle h, int32_t n, const double *X, const double
         }
         t[9] = R[b];
     }
-    return stage_bodies(h, n);
+    if (n > 0) {
+        h->half = 1 - k;
+        HIP_TRY(h, launch_take_table(stage, h->tab[1 - h->ts], kBodyStride * n, h->left, h->seen + k, ++h->ticket[k],
+                                     h->stream));
+        if (h->path == LBM_PATH_SPLIT) TRY(refresh_order(h, stage, n));
+    }
+    h->nb_next = n;
+    h->dirty = true;
+    return LBM_OK;
 }
 
 lbm_status lbm_set_bodies_device(lbm_handle h, int32_t n, const double *d_table)
@@ -1034,10 +1054,13 @@ lbm_status lbm_get_forces(lbm_handle h, double *F, double *T)
     if (st != LBM_OK) return st;
     const int nbt = h->nb_state + h->n_walls;
     if (nbt > 0 && (!F || !T)) return fail(h, LBM_ERR_ARG, "NULL output");
-    TRY(finish_forces(h, nullptr));
-    // through the pinned staging buffer: one DMA, no per-call allocation
+    // into the pinned staging buffer: by the kernel that turns the sums into
+    // forces, or, if they are there already, by a copy
     const double *buf = h->forces_pin;
-    HIP_TRY(h, hipMemcpyAsync(h->forces_pin, h->acc, sizeof(double) * 6 * nbt, hipMemcpyDeviceToHost, h->stream));
+    if (h->fpending)
+        TRY(finish_forces(h, h->forces_pin));
+    else
+        HIP_TRY(h, hipMemcpyAsync(h->forces_pin, h->acc, sizeof(double) * 6 * nbt, hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
     for (int b = 0; b < nbt; ++b)
         for (int a = 0; a < 3; ++a) {

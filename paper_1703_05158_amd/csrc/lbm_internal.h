@@ -255,6 +255,8 @@ hipError_t launch_walls_init(const uint8_t *wall, uint16_t *own, int N, hipStrea
 // of the current geometry (bodies, nb of g).
 hipError_t launch_link_records(const GeomArgs &g, const double *wrec, hipStream_t s);
 // The whole solid bitmap from the owner map (nx, ny, nz, own, bits of g).
+hipError_t launch_take_table(const double *from, double *to, int n, unsigned *left, unsigned *seen, unsigned ticket,
+                             hipStream_t s);
 hipError_t launch_mark_all(int *lost, int n, hipStream_t s);
 hipError_t launch_solid_bits(const GeomArgs &g, hipStream_t s);
 hipError_t launch_geometry(int storage, const GeomArgs &g, hipStream_t s);
