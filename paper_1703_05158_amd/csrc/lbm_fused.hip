@@ -565,10 +565,29 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) 
     fused_tile<S, TX, TY, TZ>(p, f.s.src, f.s.dst, f.s.backward ? (int)gridDim.x - 1 - t : t, lds);
 }
 
-__global__ __launch_bounds__(kBlock) void k_finish(FinishArgs fa)
+// The spheres' entries, one per thread, by the first `sphere_blocks` blocks;
+// then the walls', one per wavefront, whose lanes take the copies (a kWallRep
+// of 64): all copies in one round trip.
+__global__ __launch_bounds__(kBlock) void k_finish(FinishArgs fa, int sphere_blocks)
 {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < 6 * (fa.nb + fa.n_walls)) finish_value(fa, i);
+    static_assert(kWallRep == 64, "a lane per copy");
+    if ((int)blockIdx.x < sphere_blocks) {
+        const int i = blockIdx.x * kBlock + threadIdx.x;
+        if (i < 6 * fa.nb) finish_value(fa, i);
+        return;
+    }
+    const int e = ((int)blockIdx.x - sphere_blocks) * (kBlock / 64) + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (e >= 6 * fa.n_walls) return;
+    const int w = e / 6, c = e - 6 * w;
+    unsigned long long *p = fa.fsum + 6 * ((size_t)fa.wall_base + (size_t)w * kWallRep + lane) + c;
+    unsigned long long sum = *p;
+    *p = 0ull;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+    if (lane != 0) return;
+    const double v = (double)(long long)sum * (1.0 / kFixScale);
+    fa.out[6 * fa.nb + e] = v;
+    if (fa.out2) fa.out2[6 * fa.nb + e] = v;
 }
 
 __global__ __launch_bounds__(kBlock) void k_zero_fix(unsigned long long *p, int n)
@@ -706,9 +725,9 @@ hipError_t launch_fused(int storage, const FusedArgs &f, hipStream_t s, hipEvent
 
 hipError_t launch_finish(const FinishArgs &fa, hipStream_t s)
 {
-    const int n = 6 * (fa.nb + fa.n_walls);
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_finish, dim3(nblk(n)), dim3(kBlock), 0, s, fa);
+    const int sphere_blocks = nblk(6 * fa.nb), wall_blocks = (6 * fa.n_walls + kBlock / 64 - 1) / (kBlock / 64);
+    if (sphere_blocks + wall_blocks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_finish, dim3(sphere_blocks + wall_blocks), dim3(kBlock), 0, s, fa, sphere_blocks);
     return hipGetLastError();
 }
 

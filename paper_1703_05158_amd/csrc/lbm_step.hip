@@ -150,25 +150,36 @@ __global__ __launch_bounds__(kBlock) void k_zieb_update(ZiebArgs z)
         s_red[2][wv] = sc;
     }
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    double bu = 0.0, br = 0.0, bc = 0.0;
-    for (int w = 0; w < kW; ++w) {
-        bu += s_red[0][w];
-        br += s_red[1][w];
-        bc += s_red[2][w];
+    __shared__ bool s_last;
+    if (threadIdx.x == 0) {
+        double bu = 0.0, br = 0.0, bc = 0.0;
+        for (int w = 0; w < kW; ++w) {
+            bu += s_red[0][w];
+            br += s_red[1][w];
+            bc += s_red[2][w];
+        }
+        double *pp = z.part + 3 * (size_t)blockIdx.x;
+        __hip_atomic_store(pp, bu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(pp + 1, br, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(pp + 2, bc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // the sums are visible before the count that announces them
+        s_last = __hip_atomic_fetch_add(z.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
     }
-    double *pp = z.part + 3 * (size_t)blockIdx.x;
-    __hip_atomic_store(pp, bu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(pp + 1, br, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(pp + 2, bc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // the sums are visible before the count that announces them
-    if (__hip_atomic_fetch_add(z.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != gridDim.x - 1) return;
+    __syncthreads();
+    if (!s_last) return;
+    // the last workgroup loads all the sums at once, and one thread adds them
+    // up in workgroup order (read one after the other by that thread they took
+    // 4 of the 12 us of a 96x96 plane)
+    __shared__ double s_part[3 * kZiebMaxBlocks];
+    for (int k = threadIdx.x; k < 3 * (int)gridDim.x; k += kBlock)
+        s_part[k] = __hip_atomic_load(z.part + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
     double tu = 0.0, tr = 0.0, tc = 0.0;
     for (int b = 0; b < (int)gridDim.x; ++b) {
-        const double *q = z.part + 3 * (size_t)b;
-        tu += __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        tr += __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        tc += __hip_atomic_load(q + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        tu += s_part[3 * b];
+        tr += s_part[3 * b + 1];
+        tc += s_part[3 * b + 2];
     }
     const double vf = tc > 0.0 ? tu / tc : 0.0;
     double *st = z.state;
