@@ -331,8 +331,8 @@ lbm_status lbm_drag_gradient(lbm_handle h, int32_t nsteps, int32_t ckpt, double 
 /* Tile shape of the step kernel, the nodes of one 256-thread workgroup:
  * 0 = 64x2x2, 1 = 32x4x2, 2 = 32x2x4, 3 = 16x8x2 (x, y, z).  Results are the
  * same bit for bit for every shape; only the speed differs.  lbm_create
- * picks 64x2x2, or 32x2x4 when nx is a multiple of 32 but not of 64 and the
- * lattice has more than 512 tiles of 64x2x2.
+ * picks 64x2x2, or 32x2x4 where nx leaves clearly fewer of its lanes empty
+ * and the lattice has more than 512 tiles of 64x2x2.
  * Errors: ARG (shape out of range). */
 lbm_status lbm_set_tile(lbm_handle h, int32_t shape);
 lbm_status lbm_get_tile(lbm_handle h, int32_t *shape);

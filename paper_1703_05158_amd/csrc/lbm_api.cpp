@@ -228,6 +228,26 @@ void set_tile_shape(lbm_ctx *h, int shape)
     h->n_tiles = h->ntx * h->nty * h->ntz;
 }
 
+// The tile shape of a new lattice: 64 nodes along x, or 32 where that leaves
+// clearly fewer lanes outside the box.  FP32 tiles of 32 nodes end inside a
+// 128-byte line where nx is no multiple of 32, so they have to save more there
+// than 16-bit ones.  A lattice of few tiles takes 64x2x2 in any case: its step is
+// one workgroup's chain, which is shorter where it holds fewer nodes.  Kernel
+// times 64x2x2 / 32x2x4: 24x20x28 7.0 / 7.2 us, 32^3 7.4 / 8.4, 96^3 31 / 27,
+// 72x128x128 47 / 37, 92x91x150 40 / 37, 84^3 25 / 23, 150x100x100 42 / 44 (FP16
+// 43 / 40), 130x128x100 66 / 76 (51 / 47), 161x96x96 40 / 47 (41 / 43),
+// 96x96x256 duct 81 / 66, 160x128x128 FP16 70 / 63; 32x4x2 is nowhere ahead of
+// 32x2x4 by more than 1%.
+int default_tile(const lbm_ctx *h)
+{
+    const lbm_config &c = h->cfg;
+    const long long lanes64 = (c.nx + 63) / 64 * 64LL, lanes32 = (c.nx + 31) / 32 * 32LL;
+    const long long tiles = lanes64 / 64 * ((c.ny + 1) / 2) * ((c.nz + 1) / 2);
+    const bool saves = c.nx % 32 == 0 ? lanes32 < lanes64
+                                      : (h->sbytes == 4 ? 3 * lanes64 >= 4 * lanes32 : 5 * lanes64 >= 6 * lanes32);
+    return saves && tiles > 512 ? kTile32x2x4 : kTile64x2x2;
+}
+
 // How a step goes through memory.  Consecutive steps take the tiles in opposite
 // orders, so that a step starts on what the last one left in the 256 MiB
 // Infinity Cache (1% on the 128x128x512 duct).  The stores carry the
@@ -654,15 +674,7 @@ lbm_status lbm_create(const lbm_config *cfg, lbm_handle *out)
     };
     const size_t popb = (size_t)kQ * h->Ns * h->sbytes;
     const int nbt = c.max_bodies + c.max_walls;
-    // tile shape: 64 nodes along x, unless x is a multiple of 32 but not of 64
-    // (half of the last tile would be empty) and there are tiles enough to
-    // fill the GPU twice; below that a step is one workgroup's chain, which is
-    // shorter where it holds fewer nodes.  Kernel times 64x2x2 / 32x4x2 /
-    // 32x2x4: 24x20x28 7.0 / 7.2 / 7.2 us, 32^3 7.4 / 8.4 / 8.4, 96^3 30.3 / 29.2
-    // / 28.9, 96x96x192 48.9 / 48.9 / 48.3, 96x96x256 81 / 71 / 66, 160x128x128
-    // FP16 70 / 64 / 63.
-    set_tile_shape(h, kTile64x2x2);
-    if (c.nx % 64 != 0 && c.nx % 32 == 0 && h->n_tiles > 512) set_tile_shape(h, kTile32x2x4);
+    set_tile_shape(h, default_tile(h));
     if (dalloc(h, &h->pop[0], popb) != hipSuccess || dalloc(h, &h->pop[1], popb) != hipSuccess ||
         dalloc(h, &h->own, sizeof(uint16_t) * N + 4) != hipSuccess ||
         dalloc(h, &h->bits, sizeof(uint32_t) * (bit_row_words(c.nx) * ((size_t)c.ny * (size_t)c.nz) + kBitPad)) !=
