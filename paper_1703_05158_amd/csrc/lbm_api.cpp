@@ -18,7 +18,6 @@
 #include <map>
 #include <mutex>
 #include <new>
-#include <set>
 #include <sstream>
 #include <string>
 #include <utility>
@@ -36,8 +35,7 @@ struct lbm_ctx {
     int cur = 0;                       // pop[cur] holds the current (post-collision) state
     uint16_t *own = nullptr;
     uint32_t *bits = nullptr;          // solid bitmap of own (bit_row_words)
-    int *lost = nullptr;               // 3 * max_bodies: marks of the geometry updates, in turn (GeomArgs)
-    int lost_cur = 0;                  // which third the last update marked
+    int *lost = nullptr;               // 2 * max_bodies: marks of the geometry (GeomArgs), half ts those of tab[ts]
     void *lrec = nullptr;              // (max_walls + max_bodies) * kLinkRecBytes: link records by owner code
     uint8_t *wall_map = nullptr;
     double *tab[2] = {nullptr, nullptr};
@@ -97,6 +95,8 @@ struct lbm_ctx {
     char *grad_mem = nullptr;
     size_t grad_bytes = 0;
     int grad_dev = 0;
+    bool in_kept = false;              // linked in the list of handles that keep such memory
+    lbm_ctx *kept_prev = nullptr, *kept_next = nullptr;
     bool initialized = false;
     int steps_done = 0;
     int64_t device_bytes = 0;
@@ -158,12 +158,30 @@ hipError_t cleared(hipError_t e)
 
 // Handles that keep device memory of a finished drag gradient.  When an
 // allocation of the library fails, what they keep on that device is given
-// back and the allocation tried once more.  A handle is in the set only
-// between its calls, when no queued work uses that memory.
+// back and the allocation tried once more.  A handle is in the list only
+// outside lbm_drag_gradient, when no queued work uses that memory.  (Linked
+// through the handles: nothing is allocated and nothing can throw.)
 std::mutex kept_mutex;
-std::set<lbm_ctx *> kept;
+lbm_ctx *kept = nullptr;
 
-void give_back(lbm_ctx *h)  // kept_mutex held, or h not in the set
+void kept_add(lbm_ctx *h)  // kept_mutex held
+{
+    h->kept_prev = nullptr;
+    h->kept_next = kept;
+    if (kept) kept->kept_prev = h;
+    kept = h;
+    h->in_kept = true;
+}
+
+void kept_remove(lbm_ctx *h)  // kept_mutex held
+{
+    if (!h->in_kept) return;
+    (h->kept_prev ? h->kept_prev->kept_next : kept) = h->kept_next;
+    if (h->kept_next) h->kept_next->kept_prev = h->kept_prev;
+    h->in_kept = false;
+}
+
+void give_back(lbm_ctx *h)  // kept_mutex held, or h not in the list
 {
     if (h->grad_mem) (void)hipFree(h->grad_mem);
     h->grad_mem = nullptr;
@@ -180,14 +198,13 @@ hipError_t device_alloc(void **p, size_t bytes)
     bool freed = false;
     {
         std::lock_guard<std::mutex> lock(kept_mutex);
-        for (auto it = kept.begin(); it != kept.end();)
-            if ((*it)->grad_dev == dev) {
-                give_back(*it);
-                it = kept.erase(it);
-                freed = true;
-            } else {
-                ++it;
-            }
+        for (lbm_ctx *h = kept, *next; h; h = next) {
+            next = h->kept_next;
+            if (h->grad_dev != dev) continue;
+            kept_remove(h);
+            give_back(h);
+            freed = true;
+        }
     }
     return freed ? cleared(hipMalloc(p, bytes ? bytes : 16)) : e;
 }
@@ -430,15 +447,16 @@ lbm_status upload_wall_records(lbm_ctx *h, const double *wt, int n)
     return LBM_OK;
 }
 
-// One geometry update: the marks move on by one.
-lbm_status update_geometry(lbm_ctx *h, GeomArgs &g)
+// The marks of the geometry of tab[ts].
+int *marks(const lbm_ctx *h, int ts) { return h->lost + ts * (size_t)std::max(h->cfg.max_bodies, 1); }
+
+// Launch a geometry update to the geometry of tab[to].  The marks go with the
+// body tables, so that steps captured in a graph find them where they were.
+// (Marks left over in the array only make spheres be looked at in whole.)
+lbm_status update_geometry(lbm_ctx *h, GeomArgs &g, int to)
 {
-    const size_t cap = (size_t)std::max(h->cfg.max_bodies, 1);
-    const int prev = h->lost_cur, cur = (prev + 1) % 3, next = (prev + 2) % 3;
-    h->lost_cur = cur;
-    g.lost_prev = h->lost + prev * cap;
-    g.lost = h->lost + cur * cap;
-    g.lost_next = h->lost + next * cap;
+    g.lost_prev = marks(h, 1 - to);
+    g.lost = marks(h, to);
     HIP_TRY(h, launch_geometry(h->cfg.storage, g, h->stream));
     return LBM_OK;
 }
@@ -452,7 +470,7 @@ lbm_status rasterize_full(lbm_ctx *h)
     g.nb2 = g.nb;
     g.nb = 0;
     HIP_TRY(h, launch_walls_init(h->wall_map, h->own, h->N, h->stream));
-    TRY(update_geometry(h, g));
+    TRY(update_geometry(h, g, h->ts));
     HIP_TRY(h, launch_solid_bits(g, h->stream));
     return LBM_OK;
 }
@@ -464,7 +482,7 @@ lbm_status rasterize_update(lbm_ctx *h)
     GeomArgs g = geom(h);
     g.bodies2 = h->tab[1 - h->ts];
     g.nb2 = h->nb_next;
-    TRY(update_geometry(h, g));
+    TRY(update_geometry(h, g, 1 - h->ts));
     h->ts = 1 - h->ts;
     h->nb_state = h->nb_next;
     h->dirty = false;
@@ -679,7 +697,7 @@ lbm_status lbm_create(const lbm_config *cfg, lbm_handle *out)
         dalloc(h, &h->own, sizeof(uint16_t) * N + 4) != hipSuccess ||
         dalloc(h, &h->bits, sizeof(uint32_t) * (bit_row_words(c.nx) * ((size_t)c.ny * (size_t)c.nz) + kBitPad)) !=
             hipSuccess ||
-        dalloc(h, &h->lost, sizeof(int) * 3 * (size_t)std::max(c.max_bodies, 1)) != hipSuccess ||
+        dalloc(h, &h->lost, sizeof(int) * 2 * (size_t)std::max(c.max_bodies, 1)) != hipSuccess ||
         dalloc(h, &h->lrec, (size_t)kLinkRecBytes * std::max(nbt, 1)) != hipSuccess ||
         dalloc(h, &h->wall_map, (size_t)N) != hipSuccess ||
         dalloc(h, &h->tab[0], sizeof(double) * kBodyStride * std::max(c.max_bodies, 1)) != hipSuccess ||
@@ -704,7 +722,7 @@ lbm_status lbm_create(const lbm_config *cfg, lbm_handle *out)
     h->seen[0] = h->seen[1] = 0;
     if (hipEventCreateWithFlags(&h->stage_evt, hipEventDisableTiming) != hipSuccess) return bail(LBM_ERR_HIP);
     if (hipMemsetAsync(h->wall_map, 0, (size_t)N, h->stream) != hipSuccess ||
-        hipMemsetAsync(h->lost, 0, sizeof(int) * 3 * (size_t)std::max(c.max_bodies, 1), h->stream) != hipSuccess ||
+        hipMemsetAsync(h->lost, 0, sizeof(int) * 2 * (size_t)std::max(c.max_bodies, 1), h->stream) != hipSuccess ||
         hipMemsetAsync(h->pop[0], 0, popb, h->stream) != hipSuccess ||
         hipMemsetAsync(h->pop[1], 0, popb, h->stream) != hipSuccess ||
         hipMemsetAsync(h->acc, 0, sizeof(double) * 6 * std::max(nbt, 1), h->stream) != hipSuccess ||
@@ -728,7 +746,7 @@ void lbm_destroy(lbm_handle h)
     (void)hipStreamSynchronize(h->stream);
     {
         std::lock_guard<std::mutex> lock(kept_mutex);
-        kept.erase(h);
+        kept_remove(h);
     }
     give_back(h);
     for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
@@ -1278,8 +1296,7 @@ lbm_status lbm_set_state(lbm_handle h, const void *buf, size_t bytes)
     h->steps_done = hd.steps_done;
     HIP_TRY(h, launch_solid_bits(geom(h), h->stream));
     // which spheres own all of their balls is not part of a checkpoint
-    HIP_TRY(h, launch_mark_all(h->lost + h->lost_cur * (size_t)std::max(h->cfg.max_bodies, 1), h->cfg.max_bodies,
-                               h->stream));
+    HIP_TRY(h, launch_mark_all(marks(h, h->ts), h->cfg.max_bodies, h->stream));
     HIP_TRY(h, launch_link_records(geom(h), h->wrec, h->stream));
     h->initialized = true;
     h->geom_gen++;
@@ -1476,12 +1493,12 @@ lbm_status lbm_drag_gradient(lbm_handle h, int32_t nsteps, int32_t ckpt, double 
             h->prof = prof;
             if (h->grad_bytes > kMaxKept) give_back(h);
             std::lock_guard<std::mutex> lock(kept_mutex);
-            if (h->grad_mem) kept.insert(h);
+            if (h->grad_mem) kept_add(h);
         }
     } on_exit{h, h->prof};
     {
         std::lock_guard<std::mutex> lock(kept_mutex);
-        kept.erase(h);
+        kept_remove(h);
     }
     const bool prof = h->prof;
     // the spheres are fixed: their links are counted and listed once, each

@@ -337,7 +337,7 @@ __global__ __launch_bounds__(kBlock) void k_geometry(GeomArgs g)
     const bool mine = (lane & 1) == 0 ? b < g.nb2 : b < g.nb;
     const double *table[2] = {g.bodies2, g.bodies};
     const double *B = (lane & 1 ? g.bodies : g.bodies2) + (mine ? (size_t)b * kBodyStride : (size_t)0);
-    const int lost = b < g.nb ? g.lost_prev[b] : 0;
+    const int lost = g.lost_prev[b];
     const int ok = mine && body_ok(B, nx, ny, nz);
     const Box bx = body_box(B, 0);
     const BallCols bc = ball_cols(B, bx);
@@ -356,9 +356,9 @@ __global__ __launch_bounds__(kBlock) void k_geometry(GeomArgs g)
         invs[t] = (uint32_t)lane_of(inv, t);
     }
     // a marked sphere goes through its whole new ball
-    const bool whole = __builtin_amdgcn_readfirstlane(lost) != 0;
+    const bool whole = b < g.nb && __builtin_amdgcn_readfirstlane(lost) != 0;
     if (lane == 0) {
-        g.lost_next[b] = 0;
+        g.lost_prev[b] = 0;  // the array takes the marks of the update after this one
         if (mine) static_cast<LinkRec *>(g.lrec)[g.n_walls + b].k = sphere_k(B);
     }
     const int n_new = in_ball[0] ? box[0].ex * box[0].ey : 0;

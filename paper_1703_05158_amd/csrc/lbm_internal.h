@@ -209,10 +209,9 @@ struct GeomArgs {
     uint32_t *bits;               // the solid bitmap, kept in step with own
     void *lrec;                   // LinkRec of every solid, by owner code: the new spheres' are written
     // marks of the spheres that may not own every node of their ball (0 or
-    // 1): of the previous update (read), of this one (0 at its start) and of
-    // the next (cleared)
-    const int *lost_prev;
-    int *lost, *lost_next;
+    // 1): of the previous update (each read and cleared by its sphere's
+    // wavefront) and of this one
+    int *lost_prev, *lost;
     void *pop;
     float rho0;
 };

@@ -87,3 +87,41 @@ def test_device_tables_with_spheres_that_are_none(torch_stream):
         want = np.where(o.own >= 0, good[np.maximum(o.own, 0)], -1)
         np.testing.assert_array_equal(lat.get_owner().reshape(-1), want, err_msg=f"update {k}")
     lat.close()
+
+
+def test_overlaps_in_captured_steps(torch_stream):
+    """Two coupled steps captured in a graph and replayed with new tables in the
+    same buffers: the marks of overlapping spheres carry over from one replay to
+    the next."""
+    import oracle
+    import torch
+    from paper_1703_05158_amd import Lattice, config
+    rng = np.random.Generator(np.random.PCG64(21))
+    n, nb = (24, 22, 20), 24
+    stream = torch.cuda.Stream()
+    t = np.zeros((nb, 10))
+    t[:, 0:3] = rng.uniform(0.0, 1.0, (nb, 3)) * n
+    t[:, 9] = rng.uniform(1.0, 6.0, nb)
+    V = rng.uniform(-0.4, 0.4, (nb, 3))
+    lat = Lattice(config(*n, 0.8, 0.1, max_bodies=nb, stream=stream.cuda_stream))
+    lat.set_bodies(t[:, 0:3], t[:, 3:6], t[:, 6:9], t[:, 9])
+    lat.init_fields()
+    lat.step_noalloc(2)
+    bufs = [torch.zeros((nb, 10), dtype=torch.float64, device="cuda") for _ in range(2)]
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        for b in bufs:
+            lat.set_bodies_device(nb, b)
+            lat.step_noalloc(1)
+    o = oracle.Oracle(*n, 0.8, 0.1)
+    for k in range(8):
+        for b in bufs:
+            t[:, 0:3] = np.mod(t[:, 0:3] + V, n)
+            b.copy_(torch.from_numpy(t))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        o.set_bodies(t[:, 0:3], t[:, 3:6], t[:, 6:9], t[:, 9])
+        np.testing.assert_array_equal(lat.get_owner().reshape(-1), o.own, err_msg=f"replay {k}")
+    lat.close()
