@@ -265,16 +265,29 @@ int default_tile(const lbm_ctx *h)
     return saves && tiles > 512 ? kTile32x2x4 : kTile64x2x2;
 }
 
-// How a step goes through memory.  Consecutive steps take the tiles in opposite
-// orders, so that a step starts on what the last one left in the 256 MiB
-// Infinity Cache (1% on the 128x128x512 duct).  The stores carry the
-// non-temporal hint where the two population buffers (their bytes given) do
-// not fit in that cache; where they do, plain stores leave the next state in
-// it.  Measured, hint / plain: 128x128x512 duct FP32 (1276 MB, 30 steps) 8.35
-// / 8.70 ms, 96x96x256 duct (359 MB, 30) 3.41 / 3.55 ms, 160x128x128 box FP16
-// (200 MB, 50) 3.82 / 3.22 ms, 96^3 box (134 MB, 20) 1.72 / 1.64 ms, 48x48x160
-// duct (56 MB, 50) 1.96 / 1.89 ms.
-int stream_out(size_t bytes) { return bytes > (size_t)256 << 20; }
+// How a step goes through memory, given the bytes of its two population
+// buffers.
+//
+// The stores carry the non-temporal hint where the buffers do not fit in the
+// 256 MiB Infinity Cache, and where they fit in the 32 MiB of the eight L2
+// caches: there a step takes a few microseconds, and dirty lines that are
+// written back only when the kernel ends are waited for.  Between, plain stores
+// leave the next state in the Infinity Cache.  Measured, hint / plain:
+// 128x128x512 duct FP32 (1276 MB, 30 steps) 8.35 / 8.70 ms, 96x96x256 duct (359
+// MB, 30) 3.41 / 3.55 ms; 160x128x128 box FP16 (200 MB, 50) 3.82 / 3.22 ms,
+// 96^3 box (134 MB, 20) 0.68 / 0.58 ms, 96x48x96 (67 MB, 20) 382 / 339 us, FP16
+// (34 MB) 337 / 331 us; 96x64x64 FP16 (30 MB, 20) 369 / 378 us, 96x40x40 (23
+// MB) 288 / 306 us, 32x32x113 (18 MB) 125 / 137 us.
+//
+// Beyond the Infinity Cache consecutive steps take the tiles in opposite
+// orders, so that a step starts on what the last one left in it (1% on the
+// 128x128x512 duct).  A state that fits has no need of it, and in one order an
+// XCD finds what it wrote itself in its own L2: one order / both, 20 steps,
+// 32x32x113 137 / 175 us, 96x40x40 306 / 326 us, 96x64x64 FP16 378 / 413 us, 96^3
+// 581 / 583 us.
+constexpr size_t kL2Bytes = (size_t)32 << 20, kCacheBytes = (size_t)256 << 20;
+int stream_out(size_t bytes) { return bytes <= kL2Bytes || bytes > kCacheBytes; }
+int backward(size_t bytes, int odd) { return bytes > kCacheBytes ? odd : 0; }
 
 // Arguments of the step kernel (src/dst of the current state) and of the
 // link pass (pop of the current state, bodies of the current geometry).
@@ -292,8 +305,8 @@ StepArgs step_args(const lbm_ctx *h)
     a.nty = h->nty;
     a.ntz = h->ntz;
     a.n_tiles = h->n_tiles;
-    a.backward = h->cur;
     a.stream_out = stream_out(2 * (size_t)kQ * h->Ns * h->sbytes);
+    a.backward = backward(2 * (size_t)kQ * h->Ns * h->sbytes, h->cur);
     a.tau0 = (float)c.tau0;
     a.smag_k = (float)(18.0 * std::sqrt(2.0) * c.smag_c * c.smag_c);
     a.rho0 = (float)c.rho0;
@@ -1592,7 +1605,7 @@ lbm_status lbm_drag_gradient(lbm_handle h, int32_t nsteps, int32_t ckpt, double 
                 a.flag = nullptr;
                 a.src = state(linked);
                 a.dst = state(linked + 1);
-                a.backward = linked & 1;
+                a.backward = backward(2 * popb, linked & 1);
                 HIP_TRY(h, launch_step(c.storage, a, h->stream));
             }
         // steps m = k + 1 whose source P_k lies in the segment, m from N - 1 down
@@ -1601,7 +1614,7 @@ lbm_status lbm_drag_gradient(lbm_handle h, int32_t nsteps, int32_t ckpt, double 
             StepArgs a = step_args(h);
             a.flag = nullptr;
             a.src = state(m - 1);
-            a.backward = m & 1;
+            a.backward = backward(2 * popb, m & 1);
             AdjStepArgs ga{a, mu[li], mu[1 - li], dF_tile};
             HIP_TRY(h, launch_adj_collide(ga, h->stream));
             al.mu = mu[1 - li];
