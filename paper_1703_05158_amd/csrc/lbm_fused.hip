@@ -29,10 +29,10 @@
 // storage instruction issue.  A wavefront issues vector and scalar
 // instructions on separate ports at the same rate (one per SIMD in four
 // cycles), so both counts matter.  On the 128x128x512 duct with 4000 spheres,
-// tile 64x2x2, per wavefront: 692 vector and 599 scalar instructions (FP16),
-// 219 us per launch; with owner codes loaded per pull source and a scan over
+// tile 64x2x2, per wavefront: about 690 vector and 610 scalar instructions
+// (FP16), 209 us per launch; with owner codes loaded per pull source and a scan over
 // the workgroup (897 vector, 410 scalar, 18 loads more) it took 244 us, FP32
-// 261 against 287 us.  Masks kept per direction for the pulls as well (1305
+// 255 against 287 us.  Masks kept per direction for the pulls as well (1305
 // scalar instructions) took 316 us: the pulls therefore go to every fluid
 // lane, and the few values pulled from solid sources are replaced later.
 //
@@ -57,16 +57,23 @@ namespace {
 using namespace dev;
 
 // LDS per workgroup is held to 23040 bytes, so that seven workgroups fit in
-// a CU's 160 KB: 492 list items (on the duct 3-4.5% of the tiles hold more
-// links and take a second round) and two copies of a 16-body force table
+// a CU's 160 KB: 984 list items of 16 bits and two copies of a 16-body force
+// table
 // (with 8 bodies, tiles 64 nodes long often found the table full and sent
 // their sums to global memory)
-constexpr int kLinkCap = 492;   // links of a tile listed at once (rounds beyond)
+//
+// A tile with more links than the list holds forms them in rounds, each with
+// the masks read again and two more barriers.  With 492 items of 32 bits that
+// were 3-4.5% of the duct's tiles: 7.15 against 6.96 ms per 30 FP16 steps, 8.32
+// against 8.25 ms in FP32; on a lattice whose tiles all run at once the
+// heaviest tile sets the time, 96x40x40 with 200 spheres 288 against 256 us per
+// 20 steps.
+constexpr int kLinkCap = 984;   // links of a tile listed at once (rounds beyond)
 constexpr int kRec = 16;        // bodies of a tile with a slot in the LDS force table
 constexpr int kCopies = 2;      // copies of the table's sums (by lane), so fewer lanes add to one address
 
 struct FusedLds {
-    uint32_t item[kLinkCap];          // link: node << 24 | I << 19 | (node behind fluid) << 18
+    uint16_t item[kLinkCap];          // link: node << 6 | I << 1 | (node behind fluid)
     uint32_t val[kQ][kBlock];         // population i streamed to node n: val[i][n], as the stored value's
                                       // bits (16-bit storage: zero-extended)
     int key[kRec];                    // owner code of the body in a force slot, -1 free
@@ -259,9 +266,9 @@ __device__ __forceinline__ void wave_masks(ArgPtr f, int x0, int y, int z, const
 }
 
 // Item `it` of the tile's list: returns the link's value as the stored bits,
-// its momentum goes into the force table.  Walls are records like spheres: reference point, velocity, no
-// spin, q = 1/2 and no minimum image (their arm is about the reference
-// point).
+// its momentum goes into the force table.  Walls are records like spheres:
+// reference point, velocity, no spin, q = 1/2 and no minimum image (their arm
+// is about the reference point).
 template <int S, int TX, int TY, int TZ>
 __device__ __forceinline__ uint32_t fused_link(ArgPtr f, const typename Store<S>::T *__restrict__ src, FusedLds &lds,
                                                int x0, int y0, int z0, uint32_t it, int t)
@@ -270,8 +277,8 @@ __device__ __forceinline__ uint32_t fused_link(ArgPtr f, const typename Store<S>
     using T = typename St::T;
     const size_t Ns = (size_t)f->s.Ns;
     const int nx = f->s.nx, ny = f->s.ny, nz = f->s.nz;
-    const int nl = (int)(it >> 24), I = (int)((it >> 19) & 31u), K = I <= 9 ? I + 9 : I - 9;
-    const bool behind = (it >> 18) & 1u;
+    const int nl = (int)(it >> 6), I = (int)((it >> 1) & 31u), K = I <= 9 ? I + 9 : I - 9;
+    const bool behind = it & 1u;
     const int lx = nl % TX, ly = (nl / TX) % TY, lz = nl / (TX * TY);
     const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
     const Comp cx = comp_x(I), cy = comp_y(I), cz = comp_z(I);
@@ -432,8 +439,8 @@ __device__ __forceinline__ void fused_tile(ArgPtr f, const void *srcv, void *dst
     if (!(flags >> 20)) return;
 
     // 2. the tile's links, listed and spread over the workgroup, in rounds
-    //    of kLinkCap.  An item is node << 24 | I << 19 | (the node behind x
-    //    is fluid) << 18.  A wavefront lists its links direction by
+    //    of kLinkCap.  An item is node << 6 | I << 1 | (the node behind x
+    //    is fluid).  A wavefront lists its links direction by
     //    direction, so that neighbouring items read neighbouring nodes of
     //    the same arrays.  The value of a thread's first link waits until
     //    every pull of the tile has landed, then replaces what was pulled.
@@ -446,8 +453,8 @@ __device__ __forceinline__ void fused_tile(ArgPtr f, const void *srcv, void *dst
                 const int k = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(c >> 32),
                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)c, first + k0));
                 // the source of opp(i) is the node behind x, x + c_i
-                const uint32_t behind = __builtin_amdgcn_inverse_ballot_w64(m.cut[opp(i)]) ? 0u : 1u << 18;
-                if (all || (k >= 0 && k < kLinkCap)) lds.item[k] = (uint32_t)tid << 24 | behind | (uint32_t)i << 19;
+                const uint32_t behind = __builtin_amdgcn_inverse_ballot_w64(m.cut[opp(i)]) ? 0u : 1u;
+                if (all || (k >= 0 && k < kLinkCap)) lds.item[k] = (uint16_t)((uint32_t)tid << 6 | (uint32_t)i << 1 | behind);
             }
             k0 += __popcll(c);
         }
@@ -478,7 +485,7 @@ __device__ __forceinline__ void fused_tile(ArgPtr f, const void *srcv, void *dst
                 lds_barrier();
                 landed = true;
             }
-            if (j < n) lds.val[(it >> 19) & 31u][it >> 24] = bits;
+            if (j < n) lds.val[(it >> 1) & 31u][it >> 6] = bits;
         }
     }
     if (tot > 0) {
