@@ -154,8 +154,9 @@ __device__ __forceinline__ double min_image(double d, double L)
 __device__ __forceinline__ bool body_ok(const double *B, int nx, int ny, int nz)
 {
     const double lim = 0.5 * (double)min(nx, min(ny, nz)) - 1.0;
-    return B[9] > 0.0 && B[9] < lim && B[0] >= 0.0 && B[0] < nx && B[1] >= 0.0 && B[1] < ny &&
-           B[2] >= 0.0 && B[2] < nz;
+    // (no short cuts: the loads go out together)
+    return (B[9] > 0.0) & (B[9] < lim) & (B[0] >= 0.0) & (B[0] < nx) & (B[1] >= 0.0) & (B[1] < ny) & (B[2] >= 0.0) &
+           (B[2] < nz);
 }
 
 // Deviation of the equilibrium at rho0 and velocity u from the rest state:

@@ -1,7 +1,7 @@
 // Owner-map maintenance and state import/export kernels (gfx950).
 //
 // The owner map is kept incrementally when spheres move, in one launch with
-// one wavefront per sphere, in any order:
+// one to four wavefronts per sphere, in any order:
 //  - the sphere enters the nodes of its new ball that its old one did not
 //    cover: it takes each unless a wall or a lower-index sphere whose new ball
 //    also covers it owns it, by compare-and-swap from any other owner (a
@@ -84,7 +84,9 @@ __device__ __forceinline__ void enter_node(const GeomArgs &g, const Node &v, uin
             const int b = o - g.n_walls;
             if (b < g.nb2) {
                 const double *Bo = g.bodies2 + (size_t)b * kBodyStride;
-                if (body_ok(Bo, g.nx, g.ny, g.nz) && inside(Bo, v.px, v.py, v.pz, g.nx, g.ny, g.nz)) {
+                // (the record in one round trip: both tests without a branch)
+                const double o4[10] = {Bo[0], Bo[1], Bo[2], 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, Bo[9]};
+                if ((int)body_ok(o4, g.nx, g.ny, g.nz) & (int)inside(o4, v.px, v.py, v.pz, g.nx, g.ny, g.nz)) {
                     mark(g, id - g.n_walls);
                     return;
                 }
@@ -252,6 +254,11 @@ __device__ __forceinline__ int box_pos(int p, int x0, int n)
 }
 
 constexpr int kGeomList = 192;  // changed nodes of a wavefront taken together
+// leaving nodes of 64 from which a lane refills a whole node: 19 rounds of one
+// direction, where three nodes take one round (8 balls of radius 14 that jump:
+// 1.5 ms, three at a time 3.7 ms)
+constexpr int kManyLeft = 12;
+constexpr int kScan = 8;        // nodes of a lane whose owners are looked at together (a marked sphere's)
 
 // The n listed nodes of a wavefront change hands: sphere `id` enters or leaves
 // them.  Returns 0, the new length of the list.
@@ -276,9 +283,23 @@ __device__ __forceinline__ int work_off(const GeomArgs &g, const uint32_t *list,
                 left = true;
             }
         }
-        // refill: three nodes at a time, 19 lanes each
+        // refill: three nodes at a time, 19 lanes each, or, where many leave,
+        // a lane per node
+        uint64_t m = __ballot(left);
+        if (__popcll(m) >= kManyLeft) {
+            m = 0;
+            if (left) {
+                const Node v = node_of(list[k0 + lane] & 0x7FFFFFFFu, g.nx, g.ny);
+                double u0, u1, u2;
+                sphere_velocity(bodies + (size_t)(id - g.n_walls) * kBodyStride, v.px, v.py, v.pz, g.nx, g.ny, g.nz, u0,
+                                u1, u2);
 #pragma unroll 1
-        for (uint64_t m = __ballot(left); m;) {
+                for (int i = 0; i < kQ; ++i)
+                    St::st(at(pop + (size_t)i * g.Ns, v.n), (float)eq_dev(i, g.rho0, u0, u1, u2));
+            }
+        }
+#pragma unroll 1
+        while (m) {
             const int i = lane % kQ, third = lane / kQ;
             int from = -1;
 #pragma unroll
@@ -306,28 +327,48 @@ __device__ __forceinline__ float lane_of(float v, int l)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 
-// One wavefront per sphere.  The lanes take the (x, y) columns of the new
-// ball's box, then those of the old ball's that lie beside it; the ends of a
-// column's new and old ranges give the nodes the sphere enters and leaves
-// there, which are listed in LDS.  The list is worked off by the whole
-// wavefront: one lane per node for the owner's compare-and-swap, then one lane
-// per direction for the refills.
+// The part of an arc of length `len` from 0 on a circle of nz nodes that an
+// arc of length `other` from d (0 <= d < nz) does not cover: two runs [a1, a1 +
+// n1) and [a2, a2 + n2), exact for arcs of any lengths below nz.
+__device__ __forceinline__ void arc_less(int len, int d, int other, int nz, int &a1, int &n1, int &a2, int &n2)
+{
+    a1 = max(d + other - nz, 0);  // the other arc's part beyond nz
+    n1 = max(min(d, len) - a1, 0);
+    a2 = d + other;
+    n2 = max(len - a2, 0);
+}
+
+// 1 << lw wavefronts of a workgroup per sphere.  The lanes take the (x, y)
+// columns of the new ball's box, then those of the old ball's that lie beside
+// it; the ends of a column's new and old ranges give the nodes the sphere
+// enters and leaves there, which are listed in LDS.  A marked sphere lists
+// every node of its new ball that it does not own.  The list is worked off by
+// the whole wavefront: one lane per node for the owner's compare-and-swap, then
+// the refills.  A sphere's wavefronts take its columns in turn, 64 at a time,
+// or, where it has fewer, every second or fourth node of each column.
 // What bounds it: one wavefront's chain of sphere record, column ranges, owner
 // and compare-and-swap, through code that the step kernel's stream has pushed
 // out of the caches; hence one copy of each part, the two balls side by side
 // on two lanes, and no look at nodes that stay.  128x128x512 duct, 4000
-// spheres, about one changed node per sphere: 19.7 us; one wavefront per stamp
-// and one per vacate, each looking at every node of its ball, took 25.3 us
-// (12.1 against 11.0 us with 90 spheres, where one chain is all there is).
+// spheres, about one changed node per sphere: 25 us a step at its start, 44 us
+// 1000 steps later, when most spheres overlap.  Where a marked sphere put every
+// node of its ball on the list, and asked for a neighbour's record one value
+// after the other, 26 and 52 us; with one wavefront per stamp and one per
+// vacate, each looking at every node of its ball, 29 and 44.
 template <int S>
-__global__ __launch_bounds__(kBlock) void k_geometry(GeomArgs g)
+__global__ __launch_bounds__(kBlock) void k_geometry(GeomArgs g, int lw)
 {
     __shared__ uint32_t lists[kBlock / 64][kGeomList];  // node index, bit 31: left by the sphere
     // the sphere is the same on every lane of the wavefront: made uniform, so
     // that what follows from it is scalar
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int b = (int)blockIdx.x * (kBlock / 64) + wv;
-    if (b >= max(g.nb, g.nb2)) return;
+    const int b = ((int)blockIdx.x * (kBlock / 64) + wv) >> lw, sub = wv & ((1 << lw) - 1);
+    const bool any = b < max(g.nb, g.nb2);
+    const int lost = any ? g.lost_prev[b] : 0;
+    if (lw) __syncthreads();  // every wavefront of the sphere has read its mark
+    // a marked sphere goes through its whole new ball
+    const bool whole = b < g.nb && __builtin_amdgcn_readfirstlane(lost) != 0;
+    if (!any) return;
     const int lane = threadIdx.x & 63;
     const int nx = g.nx, ny = g.ny, nz = g.nz;
     const uint32_t plane = (uint32_t)nx * (uint32_t)ny;
@@ -337,7 +378,6 @@ __global__ __launch_bounds__(kBlock) void k_geometry(GeomArgs g)
     const bool mine = (lane & 1) == 0 ? b < g.nb2 : b < g.nb;
     const double *table[2] = {g.bodies2, g.bodies};
     const double *B = (lane & 1 ? g.bodies : g.bodies2) + (mine ? (size_t)b * kBodyStride : (size_t)0);
-    const int lost = g.lost_prev[b];
     const int ok = mine && body_ok(B, nx, ny, nz);
     const Box bx = body_box(B, 0);
     const BallCols bc = ball_cols(B, bx);
@@ -355,21 +395,21 @@ __global__ __launch_bounds__(kBlock) void k_geometry(GeomArgs g)
                            lane_of(bc.r2, t), lane_of(bc.eps2, t), lane_of(bc.m, t)};
         invs[t] = (uint32_t)lane_of(inv, t);
     }
-    // a marked sphere goes through its whole new ball
-    const bool whole = b < g.nb && __builtin_amdgcn_readfirstlane(lost) != 0;
-    if (lane == 0) {
+    if (lane == 0 && sub == 0) {
         g.lost_prev[b] = 0;  // the array takes the marks of the update after this one
         if (mine) static_cast<LinkRec *>(g.lrec)[g.n_walls + b].k = sphere_k(B);
     }
     const int n_new = in_ball[0] ? box[0].ex * box[0].ey : 0;
     const int n_cols = n_new + (in_ball[1] ? box[1].ex * box[1].ey : 0);
+    // the sphere's wavefronts: 1 << lk share each 64 columns
+    const int lk = max(lw - (n_cols > 192 ? 2 : (n_cols > 64 ? 1 : 0)), 0);
+    const int step = 1 << lk, stride = 64 << (lw - lk);
     int n = 0;  // listed nodes
-    for (int c0 = 0; c0 < n_cols; c0 += 64) {
+    for (int c0 = 64 * (sub >> lk); c0 < n_cols; c0 += stride) {
         // ---- 64 columns: the changed nodes of each
-        int e1 = 0, e2 = 0, l1 = 0, l2 = 0;                   // nodes entered and left: two runs of each
-        int ze1 = 0, ze2 = 0, zl1 = 0, zl2 = 0;               // their first z (unwrapped)
-        int start[2] = {0, 0}, len[2] = {0, 0};               // the column's ranges: wrapped start, length
-        bool every = true;                                    // the runs are exactly the changed nodes
+        int e1 = 0, e2 = 0, l1 = 0, l2 = 0;      // nodes entered and left: two runs of each
+        int ze1 = 0, ze2 = 0, zl1 = 0, zl2 = 0;  // their first z (from that of the range)
+        int start[2] = {0, 0}, len[2] = {0, 0};  // the column's ranges: wrapped start, length
         uint32_t col = 0;
         const int c = c0 + lane;
         if (c < n_cols) {
@@ -382,12 +422,6 @@ __global__ __launch_bounds__(kBlock) void k_geometry(GeomArgs g)
             }
             const int px = wrap1((t0 ? box[1].x0 : box[0].x0) + kx, nx), py = wrap1((t0 ? box[1].y0 : box[0].y0) + ky, ny);
             col = (uint32_t)px + (uint32_t)nx * (uint32_t)py;
-            int a[2], e[2];
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                a[t] = 1;
-                e[t] = 0;
-            }
             const bool in_new = in_ball[0] && box_pos(px, box[0].x0, nx) < box[0].ex && box_pos(py, box[0].y0, ny) < box[0].ey;
             if (!(t0 && in_new)) {  // (an old column inside the new box was taken with the new ones)
 #pragma unroll 1
@@ -398,65 +432,64 @@ __global__ __launch_bounds__(kBlock) void k_geometry(GeomArgs g)
                         int lo, hi;
                         column_range(table[t] + (size_t)b * kBodyStride, bt, t ? cols[1] : cols[0], qx, qy, px, py, nx, ny,
                                      nz, lo, hi);
+                        const int at0 = wrap1(lo, nz), m = max(hi - lo + 1, 0);
                         if (t) {
-                            a[1] = lo;
-                            e[1] = max(hi, lo - 1);
+                            start[1] = at0;
+                            len[1] = m;
                         } else {
-                            a[0] = lo;
-                            e[0] = max(hi, lo - 1);
+                            start[0] = at0;
+                            len[0] = m;
                         }
                     }
                 }
             }
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                start[t] = wrap1(a[t], nz);
-                len[t] = e[t] - a[t] + 1;
-            }
-            // the old range in the new one's frame, at the nearest image:
-            // ranges of at most half the axis each meet at no other image
-            int d = start[1] - start[0];
-            if (2 * d > nz) d -= nz;
-            else if (2 * d <= -nz) d += nz;
-            const int oa = a[0] + d, oe = oa + len[1] - 1;
-            every = 2 * len[0] <= nz && 2 * len[1] <= nz;
-            ze1 = a[0];
-            zl1 = oa;
-            if (!every) {  // all of both ranges, each node then tested against the other
-                e1 = len[0];
-                l1 = len[1];
-            } else {
-                ze2 = max(a[0], oe + 1);
-                zl2 = max(oa, e[0] + 1);
-                e1 = max(0, min(e[0], oa - 1) - ze1 + 1);
-                e2 = max(0, e[0] - ze2 + 1);
-                l1 = max(0, min(oe, a[0] - 1) - zl1 + 1);
-                l2 = max(0, oe - zl2 + 1);
-            }
-            if (whole) {
-                e1 = len[0];
-                e2 = 0;
-            }
+            const int d = start[1] - start[0];
+            arc_less(len[0], d < 0 ? d + nz : d, len[1], nz, ze1, e1, ze2, e2);
+            arc_less(len[1], d > 0 ? nz - d : -d, len[0], nz, zl1, l1, zl2, l2);
+            if (whole) e1 = e2 = 0;  // (looked at with the rest of the ball)
         }
-        // ---- listed, one node of each column at a time
-        const int cnt = e1 + e2 + l1 + l2;
-        for (int k = 0;; ++k) {
+        // ---- listed, one node of each column at a time: the changed nodes,
+        //      then those of a marked sphere's ball that are not its own
+        const int cnt = e1 + e2 + l1 + l2, scan = whole ? len[0] : 0;
+        uint32_t todo = 0;
+        int k = sub & (step - 1), ks = k - kScan * step;
+        while (true) {
             // ---- the listed nodes change hands when the list is full or
             //      there are no more
-            const bool more = __ballot(k < cnt) != 0;
-            if (n > kGeomList - 64 || (!more && n && c0 + 64 >= n_cols)) n = work_off<S>(g, list, n, id, g.bodies, lane);
+            const bool runs = __ballot(k < cnt) != 0;
+            const bool more = runs || __ballot(todo != 0 || ks + kScan * step < scan) != 0;
+            if (n > kGeomList - 64 || (!more && n && c0 + stride >= n_cols)) n = work_off<S>(g, list, n, id, g.bodies, lane);
             if (!more) break;
-            const bool leaves = k >= e1 + e2;
-            const int z = k < e1 ? ze1 + k
-                                 : (!leaves ? ze2 + (k - e1) : (k < e1 + e2 + l1 ? zl1 + (k - e1 - e2) : zl2 + (k - e1 - e2 - l1)));
-            const int pz = wrap1(z, nz);
-            bool changed = k < cnt;
-            if (!every && changed && (leaves || !whole))
-                changed = box_pos(pz, leaves ? start[0] : start[1], nz) >= (leaves ? len[0] : len[1]);
+            bool changed, leaves = false;
+            int z;
+            if (runs) {
+                leaves = k >= e1 + e2;
+                z = k < e1 ? ze1 + k
+                           : (!leaves ? ze2 + (k - e1) : (k < e1 + e2 + l1 ? zl1 + (k - e1 - e2) : zl2 + (k - e1 - e2 - l1)));
+                changed = k < cnt;
+                k += step;
+            } else {
+                if (!__ballot(todo != 0)) {
+                    ks += kScan * step;
+                    uint16_t o[kScan];
+#pragma unroll
+                    for (int u = 0; u < kScan; ++u) {
+                        const int q = ks + u * step;
+                        o[u] = id;
+                        if (q < scan) o[u] = *at(g.own, col + plane * (uint32_t)wrap1(start[0] + q, nz));
+                    }
+#pragma unroll
+                    for (int u = 0; u < kScan; ++u) todo |= (o[u] != id && o[u] >= g.n_walls) ? 1u << u : 0u;
+                }
+                changed = todo != 0;
+                z = ks + (changed ? __builtin_ctz(todo) : 0) * step;
+                todo &= todo - 1u;
+            }
+            const uint32_t node = col + plane * (uint32_t)wrap1((leaves ? start[1] : start[0]) + z, nz);
             const uint64_t m = __ballot(changed);
             if (changed)
                 list[n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
-                    (col + plane * (uint32_t)pz) | (leaves ? 0x80000000u : 0u);
+                    node | (leaves ? 0x80000000u : 0u);
             n += __popcll(m);
         }
     }
@@ -583,6 +616,18 @@ __global__ __launch_bounds__(kBlock) void k_count_fluid(const uint16_t *own, int
 
 inline int nblk(long n) { return (int)((n + kBlock - 1) / kBlock); }
 
+// Wavefronts of k_geometry per sphere, as a power of two: as many as the chip
+// holds at once (its registers leave four to each of 1024 SIMDs), up to four.
+// Few spheres leave most of it idle while a large, jumping or overlapped one
+// makes a long chain; with many, each wavefront's set-up is what costs.  us per
+// update with 1 / 2 / 4 wavefronts: one sphere of radius 30 in 96^3 239 / 132 / 72, 60
+// of radius 8 to 14, most overlapping, 342 / 181 / 106; radius 4, 300 spheres
+// 18.6 / 17.0 / 16.2, jumping 61 / 39 / 37, 1000 spheres 22.0 / 21.6 / 21.0; radius 3,
+// 2000 spheres 21.6 / 22.0 / 26.5; the duct's 4000, in whole steps, 275.7 / 278.3 /
+// 279.6; radius 2, 8000 spheres 29 / 40 / 59.
+constexpr int kGeomWaves = 4096;
+inline int geometry_split(int spheres) { return spheres <= kGeomWaves / 4 ? 2 : (spheres <= kGeomWaves / 2 ? 1 : 0); }
+
 template <template <int> class K, typename... A>
 hipError_t dispatch(int storage, dim3 grid, dim3 block, hipStream_t s, A... args)
 {
@@ -643,8 +688,8 @@ hipError_t launch_geometry(int storage, const GeomArgs &g, hipStream_t s)
 {
     const int spheres = std::max(g.nb, g.nb2);
     if (spheres <= 0) return hipSuccess;
-    const int grid = (spheres + kBlock / 64 - 1) / (kBlock / 64);
-    return dispatch<GeomK>(storage, dim3(grid), dim3(kBlock), s, g);
+    const int lw = geometry_split(spheres), per_block = (kBlock / 64) >> lw;
+    return dispatch<GeomK>(storage, dim3((spheres + per_block - 1) / per_block), dim3(kBlock), s, g, lw);
 }
 
 hipError_t launch_init_pop(int storage, const GeomArgs &g, const double *rho, const double *u, hipStream_t s)
