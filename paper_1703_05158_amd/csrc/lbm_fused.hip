@@ -73,7 +73,7 @@ constexpr int kRec = 16;        // bodies of a tile with a slot in the LDS force
 constexpr int kCopies = 2;      // copies of the table's sums (by lane), so fewer lanes add to one address
 
 struct FusedLds {
-    uint16_t item[kLinkCap];          // link: node << 6 | I << 1 | (node behind fluid)
+    uint16_t item[kLinkCap];          // link: node << 6 | I << 1 | (node behind solid)
     uint32_t val[kQ][kBlock];         // population i streamed to node n: val[i][n], as the stored value's
                                       // bits (16-bit storage: zero-extended)
     int key[kRec];                    // owner code of the body in a force slot, -1 free
@@ -170,16 +170,22 @@ __device__ __forceinline__ int quick_div(int t, int d, uint32_t inv, int &rem)
     return q;
 }
 
+typedef uint32_t uint32x2 __attribute__((ext_vector_type(2)));
+
 // A wavefront's share of a tile, 64 / TX rows of TX nodes at z from row y on,
 // as 64-bit lane masks in scalar registers: the lanes inside the lattice,
 // those of fluid nodes, and per direction the fluid lanes whose pull source
 // x - c_i is solid (a cut link).  Everything here is scalar: the windows of
 // the solid bitmap are scalar loads, a direction's mask is a shift of one of
 // them, and using a mask as the lanes of a load or store costs no vector
-// instruction.
+// instruction.  Scalar instructions count as vector ones do (see above): on
+// lattices whose tiles all run at once the chain through them is what a step
+// waits for.  With the masks set to zero where there are no links and 32-node
+// rows combined by 64-bit shifts, 60 more per wavefront, 96x40x40 with 204
+// spheres took 255 against 245 us per 20 steps (FP16 259 / 250), 160x128x128 FP16
+// 3.14 against 3.01 ms per 50.
 template <int TX>
 struct WaveMasks {
-    static constexpr int kRows = 64 / TX;
     uint64_t in, fluid, cut[kQ];
 };
 
@@ -201,8 +207,9 @@ struct WaveRows {
     }
 };
 
+// Returns whether the wavefront has links; without any, cut is left unset.
 template <int TX>
-__device__ __forceinline__ void wave_masks(ArgPtr f, int x0, int y, int z, const WaveRows<64 / TX> &w,
+__device__ __forceinline__ bool wave_masks(ArgPtr f, int x0, int y, int z, const WaveRows<64 / TX> &w,
                                            WaveMasks<TX> &m)
 {
     constexpr int R = 64 / TX;
@@ -216,9 +223,7 @@ __device__ __forceinline__ void wave_masks(ArgPtr f, int x0, int y, int z, const
     for (int r = 0; r < R; ++r)
         if (z < nz && y + r < ny) m.in |= row_in << (r * TX & 63);
     m.fluid = 0;
-#pragma unroll
-    for (int i = 1; i < kQ; ++i) m.cut[i] = 0;
-    if (!m.in) return;
+    if (!m.in) return false;
     const uint32_t rw = 4u * (uint32_t)bit_row_words(nx);
     const ScalarPtr bits = (ScalarPtr)(uintptr_t)f->bits;
     uint32_t yw[R + 2];  // byte offsets of the rows' windows within a plane
@@ -244,6 +249,10 @@ __device__ __forceinline__ void wave_masks(ArgPtr f, int x0, int y, int z, const
         return (lo[dz][k] >> (half + s)) & kOnes;
     };
     auto rows = [&](int cx, int cy, int cz) {  // solid bits of the sources x - c of the wavefront's nodes
+        if constexpr (TX == 32) {  // two registers side by side, nothing to shift and combine
+            const uint32_t a = (uint32_t)(lo[1 - cz][1 - cy] >> (1 - cx)), b = (uint32_t)(lo[1 - cz][2 - cy] >> (1 - cx));
+            return __builtin_bit_cast(uint64_t, uint32x2{a, b});
+        }
         uint64_t v = 0;
 #pragma unroll
         for (int r = 0; r < R; ++r) v |= window(1 - cz, r + 1 - cy, 1 - cx) << (r * TX & 63);
@@ -260,9 +269,10 @@ __device__ __forceinline__ void wave_masks(ArgPtr f, int x0, int y, int z, const
             any |= lo[dz][k];
             any_hi |= hi[dz][k];
         }
-    if (!(any | any_hi)) return;
+    if (!(any | any_hi)) return false;
 #pragma unroll
     for (int i = 1; i < kQ; ++i) m.cut[i] = m.fluid & rows(CX[i], CY[i], CZ[i]);
+    return true;
 }
 
 // Item `it` of the tile's list: returns the link's value as the stored bits,
@@ -278,7 +288,7 @@ __device__ __forceinline__ uint32_t fused_link(ArgPtr f, const typename Store<S>
     const size_t Ns = (size_t)f->s.Ns;
     const int nx = f->s.nx, ny = f->s.ny, nz = f->s.nz;
     const int nl = (int)(it >> 6), I = (int)((it >> 1) & 31u), K = I <= 9 ? I + 9 : I - 9;
-    const bool behind = it & 1u;
+    const bool behind = !(it & 1u);  // the node behind is fluid
     const int lx = nl % TX, ly = (nl / TX) % TY, lz = nl / (TX * TY);
     const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
     const Comp cx = comp_x(I), cy = comp_y(I), cz = comp_z(I);
@@ -396,7 +406,7 @@ __device__ __forceinline__ void fused_tile(ArgPtr f, const void *srcv, void *dst
     // 1. which lanes are fluid, and which directions of each are cut
     const WaveRows<R> rows(wy, z, ny, nz);
     WaveMasks<TX> mk;
-    wave_masks<TX>(f, x0, wy, z, rows, mk);
+    const bool links = wave_masks<TX>(f, x0, wy, z, rows, mk);
     // byte offsets of the lane's pull sources x - c_i within a direction's
     // array (below 2^32): a lane part for the x neighbour and, where the
     // wavefront holds several rows, the y neighbour, and a scalar part for
@@ -422,8 +432,9 @@ __device__ __forceinline__ void fused_tile(ArgPtr f, const void *srcv, void *dst
     const bool inflow = z == f->s.zieb_z;
     auto links_of = [&](const WaveMasks<TX> &m, int i) -> uint64_t { return inflow && CZ[i] == 1 ? 0ull : m.cut[i]; };
     int cnt = 0;
+    if (links)
 #pragma unroll
-    for (int i = 1; i < kQ; ++i) cnt += __popcll(links_of(mk, i));
+        for (int i = 1; i < kQ; ++i) cnt += __popcll(links_of(mk, i));
     for (int k = tid; k < kRec; k += kBlock) lds.key[k] = -1;
     for (int k = tid; k < kCopies * kRec * 6; k += kBlock) (&lds.sum[0][0][0])[k] = 0ull;
     if (lane == 0) lds.wtot[wv] = cnt | (mk.fluid ? 1 << 20 : 0);  // cnt <= 64 * 18
@@ -440,7 +451,7 @@ __device__ __forceinline__ void fused_tile(ArgPtr f, const void *srcv, void *dst
 
     // 2. the tile's links, listed and spread over the workgroup, in rounds
     //    of kLinkCap.  An item is node << 6 | I << 1 | (the node behind x
-    //    is fluid).  A wavefront lists its links direction by
+    //    is solid).  A wavefront lists its links direction by
     //    direction, so that neighbouring items read neighbouring nodes of
     //    the same arrays.  The value of a thread's first link waits until
     //    every pull of the tile has landed, then replaces what was pulled.
@@ -453,8 +464,8 @@ __device__ __forceinline__ void fused_tile(ArgPtr f, const void *srcv, void *dst
                 const int k = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(c >> 32),
                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)c, first + k0));
                 // the source of opp(i) is the node behind x, x + c_i
-                const uint32_t behind = __builtin_amdgcn_inverse_ballot_w64(m.cut[opp(i)]) ? 0u : 1u;
-                if (all || (k >= 0 && k < kLinkCap)) lds.item[k] = (uint16_t)((uint32_t)tid << 6 | (uint32_t)i << 1 | behind);
+                const uint32_t solid = __builtin_amdgcn_inverse_ballot_w64(m.cut[opp(i)]) ? 1u : 0u;
+                if (all || (k >= 0 && k < kLinkCap)) lds.item[k] = (uint16_t)((uint32_t)tid << 6 | (uint32_t)i << 1 | solid);
             }
             k0 += __popcll(c);
         }
@@ -468,8 +479,7 @@ __device__ __forceinline__ void fused_tile(ArgPtr f, const void *srcv, void *dst
         if (base) {
             lds_barrier();  // the previous round's list is processed
             WaveMasks<TX> again;  // (not kept: few tiles need a second round)
-            wave_masks<TX>(reread(f), x0, wy, z, WaveRows<R>(wy, z, ny, nz), again);
-            list(again, base, false);
+            if (wave_masks<TX>(reread(f), x0, wy, z, WaveRows<R>(wy, z, ny, nz), again)) list(again, base, false);
         }
         lds_barrier();  // the list is written (an LDS-only barrier: the pulls stay in flight)
         const int n = min(kLinkCap, tot - base);
