@@ -1527,17 +1527,14 @@ lbm_status lbm_drag_gradient(lbm_handle h, int32_t nsteps, int32_t ckpt, double 
         TRY(copy_sync(h, cnt.data(), d_first, sizeof(int) * (size_t)nb, hipMemcpyDeviceToHost));
     }
     SphereLinks links{};
-    std::vector<uint32_t> sphere;
     for (int b = 0; b < nb; ++b) {
         first[(size_t)b] = links.n;
-        const int waves = (cnt[(size_t)b] + 63) / 64;
-        links.n += 64 * waves;
-        sphere.insert(sphere.end(), (size_t)waves, (uint32_t)b);
+        links.n += (cnt[(size_t)b] + 63) / 64 * 64;
     }
     const size_t list = sizeof(uint32_t) * (size_t)links.n, sums = sizeof(double) * 3 * (size_t)h->n_tiles;
-    const size_t dVb = sizeof(double) * 3 * (size_t)std::max(nb, 1);
+    const size_t dVb = sizeof(double) * 3 * (size_t)std::max(nb, 1), dWb = sizeof(double) * 3 * (size_t)(links.n / 64);
     TRY(gradient_memory(h, firsts + (size_t)(nck + nseg - 1 + 2) * popb + 6 * pad(list) +
-                               pad(sizeof(uint32_t) * sphere.size()) + pad(sums) + pad(sizeof(double) * 3) + pad(dVb),
+                               pad(dWb) + pad(sums) + pad(sizeof(double) * 3) + pad(dVb),
                         nck, nseg));
     int *d_first = reinterpret_cast<int *>(h->grad_mem);
     char *mem = h->grad_mem + firsts;
@@ -1553,14 +1550,14 @@ lbm_status lbm_drag_gradient(lbm_handle h, int32_t nsteps, int32_t ckpt, double 
     float *mu[2] = {reinterpret_cast<float *>(take(popb)), reinterpret_cast<float *>(take(popb))};
     for (uint32_t **p : {&links.x, &links.p, &links.b, &links.code}) *p = reinterpret_cast<uint32_t *>(take(list));
     for (float **p : {&links.q, &links.mw}) *p = reinterpret_cast<float *>(take(list));
-    links.sphere = reinterpret_cast<uint32_t *>(take(sizeof(uint32_t) * sphere.size()));
+    double *dW = reinterpret_cast<double *>(take(dWb));
     double *dF_tile = reinterpret_cast<double *>(take(sums));
     double *dF = reinterpret_cast<double *>(take(sizeof(double) * 3));
     double *dV = reinterpret_cast<double *>(take(dVb));
     if (links.n > 0) {
         HIP_TRY(h, hipMemsetAsync(links.code, 0, list, h->stream));
+        HIP_TRY(h, hipMemsetAsync(dW, 0, dWb, h->stream));
         TRY(copy_sync(h, d_first, first.data(), sizeof(int) * (size_t)nb, hipMemcpyHostToDevice));
-        TRY(copy_sync(h, links.sphere, sphere.data(), sizeof(uint32_t) * sphere.size(), hipMemcpyHostToDevice));
         HIP_TRY(h, launch_fill_links(lg, links, d_first, h->stream));
     }
     const lbm_config &c = h->cfg;
@@ -1586,9 +1583,8 @@ lbm_status lbm_drag_gradient(lbm_handle h, int32_t nsteps, int32_t ckpt, double 
     for (int b = 0; b < nb; ++b) Jv += acc_h[(size_t)6 * b];
     // backward: the objective's derivative gives the adjoint of P_{N-1}
     HIP_TRY(h, hipMemsetAsync(dF_tile, 0, sums, h->stream));
-    HIP_TRY(h, hipMemsetAsync(dV, 0, dVb, h->stream));
     HIP_TRY(h, hipMemsetAsync(mu[0], 0, popb, h->stream));
-    AdjLinkArgs al{links, h->Ns, (float)c.rho0, mu[0], dV};
+    AdjLinkArgs al{links, h->Ns, (float)c.rho0, mu[0], dW};
     HIP_TRY(h, launch_adj_links(al, true, h->stream));
     int li = 0;  // mu[li] belongs to the step after the next reverse one
     for (int s = nck - 1; s >= 0; --s) {
@@ -1623,6 +1619,7 @@ lbm_status lbm_drag_gradient(lbm_handle h, int32_t nsteps, int32_t ckpt, double 
         }
     }
     HIP_TRY(h, launch_adj_reduce(dF_tile, h->n_tiles, dF, h->stream));
+    HIP_TRY(h, launch_adj_dv(dW, d_first, links.n, nb, dV, h->stream));
     TRY(copy_sync(h, dJdF, dF, sizeof(double) * 3, hipMemcpyDeviceToHost));
     if (nb > 0) TRY(copy_sync(h, dJdV, dV, sizeof(double) * 3 * nb, hipMemcpyDeviceToHost));
     *J = Jv;

@@ -184,7 +184,6 @@ struct SphereLinks {
     uint32_t *x, *p, *b;          // the fluid node, the solid node x + c_K, the node behind x + c_I
     uint32_t *code;               // I | (node behind fluid) << 5 | 1 << 6 | (second to its shared slot) << 7; 0: padding
     float *q, *mw;                // link fraction and moving-boundary term, as the step forms them
-    uint32_t *sphere;             // [n / 64]: the wavefront's sphere
     int n;                        // padded length
 };
 
@@ -193,7 +192,7 @@ struct AdjLinkArgs {
     int Ns;
     float rho0;
     float *mu;                    // adjoint of the streamed populations, [19][Ns]
-    double *dV;                   // [nb][3], accumulated over the steps
+    double *dW;                   // [n / 64][3]: each wavefront's part of dJ/dV, accumulated over the steps
 };
 
 struct GeomArgs {
@@ -248,6 +247,9 @@ hipError_t launch_listed_links(const SphereLinks &l, float *pop, int Ns, hipStre
 // The links' part of a reverse step (objective: of J itself).
 hipError_t launch_adj_links(const AdjLinkArgs &g, bool objective, hipStream_t s);
 hipError_t launch_adj_reduce(const double *dF_tile, int n_tiles, double *dF, hipStream_t s);
+// dJ/dV of each of nb spheres from its wavefronts' parts; sphere b's links begin
+// at first[b], n in all.
+hipError_t launch_adj_dv(const double *dW, const int *first, int n, int nb, double *dV, hipStream_t s);
 
 hipError_t launch_walls_init(const uint8_t *wall, uint16_t *own, int N, hipStream_t s);
 // Link records of the walls (wrec: [n_walls][kBodyStride]) and of the spheres

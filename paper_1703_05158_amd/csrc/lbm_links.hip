@@ -569,7 +569,8 @@ __global__ __launch_bounds__(kBlock) void k_listed_links(SphereLinks l, float *p
 }
 
 // One thread per link; a wavefront's links are one sphere's, whose part of
-// dJ/dV they add up.
+// dJ/dV they add to the wavefront's own entry (k_adj_dv adds these up in order:
+// the sums are the same every time).
 template <bool kObjective>
 __global__ __launch_bounds__(kBlock) void k_adj_links(AdjLinkArgs g)
 {
@@ -579,6 +580,9 @@ __global__ __launch_bounds__(kBlock) void k_adj_links(AdjLinkArgs g)
     const int e = blockIdx.x * kBlock + threadIdx.x;
     if (e >= l.n) return;  // whole wavefronts: n is a multiple of 64
     const uint32_t code = l.code[e];
+    const int lane = threadIdx.x & 63;
+    double *const part = g.dW + 3 * (size_t)(e >> 6) + lane;  // of lanes 0 to 2
+    const double before = lane < 3 ? *part : 0.0;
     double acc[3] = {0.0, 0.0, 0.0};
     if (code) {
         const int I = (int)(code & 31u), K = opp(I);
@@ -608,10 +612,24 @@ __global__ __launch_bounds__(kBlock) void k_adj_links(AdjLinkArgs g)
     for (int off = 32; off > 0; off >>= 1)
 #pragma unroll
         for (int c = 0; c < 3; ++c) acc[c] += __shfl_xor(acc[c], off);
-    if ((threadIdx.x & 63) < 3) {
-        const int c = threadIdx.x & 63;
-        atomicAdd(g.dV + 3 * (size_t)l.sphere[e >> 6] + c, c == 0 ? acc[0] : (c == 1 ? acc[1] : acc[2]));
-    }
+    if (lane < 3) *part = before + (lane == 0 ? acc[0] : (lane == 1 ? acc[1] : acc[2]));
+}
+
+// One wavefront per sphere: its wavefronts' parts, a lane every 64th, then the
+// lanes' sums.
+__global__ __launch_bounds__(64) void k_adj_dv(const double *dW, const int *first, int n, int nb, double *dV)
+{
+    const int b = blockIdx.x;
+    const int w1 = (b + 1 < nb ? first[b + 1] : n) / 64;
+    double acc[3] = {0.0, 0.0, 0.0};
+    for (int w = first[b] / 64 + (int)threadIdx.x; w < w1; w += 64)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) acc[c] += dW[3 * (size_t)w + c];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) acc[c] += __shfl_xor(acc[c], off);
+    if (threadIdx.x < 3) dV[3 * (size_t)b + threadIdx.x] = threadIdx.x == 0 ? acc[0] : (threadIdx.x == 1 ? acc[1] : acc[2]);
 }
 
 // The parts that come second.
@@ -670,6 +688,13 @@ hipError_t launch_adj_links(const AdjLinkArgs &g, bool objective, hipStream_t s)
         hipLaunchKernelGGL(k_adj_links<false>, grid, dim3(kBlock), 0, s, g);
         hipLaunchKernelGGL(k_adj_second<false>, grid, dim3(kBlock), 0, s, g);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_adj_dv(const double *dW, const int *first, int n, int nb, double *dV, hipStream_t s)
+{
+    if (nb <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_adj_dv, dim3(nb), dim3(64), 0, s, dW, first, n, nb, dV);
     return hipGetLastError();
 }
 
