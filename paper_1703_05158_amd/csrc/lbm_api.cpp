@@ -99,7 +99,7 @@ struct lbm_ctx {
     lbm_ctx *kept_prev = nullptr, *kept_next = nullptr;
     bool initialized = false;
     int steps_done = 0;
-    int64_t device_bytes = 0;
+    int64_t device_bytes = 0;          // without grad_bytes, which other threads may change (see kept)
     bool prof = false;
     int prof_every = 1;                // profile every prof_every-th step
     int64_t prof_n = 0;                // steps since profiling was switched on
@@ -160,7 +160,10 @@ hipError_t cleared(hipError_t e)
 // allocation of the library fails, what they keep on that device is given
 // back and the allocation tried once more.  A handle is in the list only
 // outside lbm_drag_gradient, when no queued work uses that memory.  (Linked
-// through the handles: nothing is allocated and nothing can throw.)
+// through the handles: nothing is allocated and nothing can throw.)  The thread
+// whose allocation fails changes grad_mem and grad_bytes of a listed handle, and
+// nothing else of it, under the mutex: a handle's own thread looks at them
+// under it too.
 std::mutex kept_mutex;
 lbm_ctx *kept = nullptr;
 
@@ -185,7 +188,6 @@ void give_back(lbm_ctx *h)  // kept_mutex held, or h not in the list
 {
     if (h->grad_mem) (void)hipFree(h->grad_mem);
     h->grad_mem = nullptr;
-    h->device_bytes -= (int64_t)h->grad_bytes;
     h->grad_bytes = 0;
 }
 
@@ -1327,7 +1329,8 @@ lbm_status lbm_get_info(lbm_handle h, lbm_info *info)
     info->n_walls = h->n_walls;
     info->storage_bytes = h->sbytes;
     info->steps_done = h->steps_done;
-    info->device_bytes = h->device_bytes;
+    std::lock_guard<std::mutex> lock(kept_mutex);
+    info->device_bytes = h->device_bytes + (int64_t)h->grad_bytes;
     return LBM_OK;
 }
 
@@ -1472,7 +1475,6 @@ lbm_status gradient_memory(lbm_ctx *h, size_t bytes, int nck, int nseg)
         return fail(h, LBM_ERR_OOM, "no device memory for %d checkpoints and %d recomputed states", nck, nseg);
     h->grad_mem = static_cast<char *>(p);
     h->grad_bytes = bytes;
-    h->device_bytes += (int64_t)bytes;
     HIP_TRY(h, hipGetDevice(&h->grad_dev));
     return LBM_OK;
 }
