@@ -1836,10 +1836,10 @@ lbm_status batch_build(lbm_batch_ctx *b)
         forces += 6 * (h->nb_state + h->n_walls);
         b->gen[(size_t)i] = h->geom_gen;
     }
-    BHIP_TRY(b, cleared(hipMalloc((void **)&b->d_members, sizeof(BatchMember) * (size_t)n)));
-    if (!b->d_cur) BHIP_TRY(b, cleared(hipMalloc((void **)&b->d_cur, sizeof(int) * (size_t)n)));
+    BHIP_TRY(b, device_alloc((void **)&b->d_members, sizeof(BatchMember) * (size_t)n));
+    if (!b->d_cur) BHIP_TRY(b, device_alloc((void **)&b->d_cur, sizeof(int) * (size_t)n));
     if (!b->d_queue) {
-        BHIP_TRY(b, cleared(hipMalloc((void **)&b->d_queue, sizeof(int) * kQueueInts)));
+        BHIP_TRY(b, device_alloc((void **)&b->d_queue, sizeof(int) * kQueueInts));
         BHIP_TRY(b, hipMemsetAsync(b->d_queue, 0, sizeof(int) * kQueueInts, b->stream));
     }
     if (!b->h_cur) BHIP_TRY(b, cleared(hipHostMalloc((void **)&b->h_cur, sizeof(int) * (size_t)n)));

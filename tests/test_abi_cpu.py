@@ -177,3 +177,17 @@ def test_oracle_stays_out_of_the_product():
            and ("oracle" in [a.name.split(".")[0] for a in n.names] or (getattr(n, "module", "") or "").startswith("oracle"))]
     assert not top
     assert users == ["cpu_baseline"]
+
+
+def test_device_memory_comes_from_one_place(P):
+    """Every device allocation of the library goes through device_alloc, which
+    gives back what handles keep from a drag gradient before it fails."""
+    csrc = os.path.join(ROOT, "paper_1703_05158_amd", "csrc")
+    calls = []
+    for f in sorted(os.listdir(csrc)):
+        txt = open(os.path.join(csrc, f)).read()
+        calls += [f] * len(re.findall(r"\bhipMalloc(?:Async|Managed|Pitch)?\s*\(", txt))
+    txt = open(os.path.join(csrc, "lbm_api.cpp")).read()
+    body = txt[txt.index("hipError_t device_alloc("):]
+    body = body[:body.index("\n}\n")]
+    assert calls == ["lbm_api.cpp"] * len(re.findall(r"\bhipMalloc\s*\(", body))
