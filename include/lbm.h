@@ -321,12 +321,17 @@ lbm_status lbm_set_body_force(lbm_handle h, const double *F);
  * min(ckpt, nsteps) + 1 population buffers and 24.4 bytes per cut link, each
  * sphere's links counted in whole 64s.  The handle keeps it for the next
  * gradient if it is no more than 8 GiB (counted in lbm_info.device_bytes); it
- * is freed with the handle, or when an allocation of device memory by the
- * library would fail otherwise.  The same call on the same state gives the same gradient, bit for
- * bit.  Needs FP32 storage, no walls and no inflow plane.  Synchronises.
+ * is freed with the handle, when an allocation of device memory by the library
+ * would fail otherwise, or by lbm_release_memory, for the process's other
+ * allocators.  The same call on the same state gives the same gradient, bit
+ * for bit.  Needs FP32 storage, no walls and no inflow plane.  Synchronises.
  * Errors: ARG, STATE, OOM, HIP. */
 lbm_status lbm_drag_gradient(lbm_handle h, int32_t nsteps, int32_t ckpt, double *J, double *dJdF,
                              double *dJdV);
+
+/* Free the device memory that the handle keeps from its last drag gradient, if
+ * any (the next one allocates again).  Errors: ARG. */
+lbm_status lbm_release_memory(lbm_handle h);
 
 /* Tile shape of the step kernel, the nodes of one 256-thread workgroup:
  * 0 = 64x2x2, 1 = 32x4x2, 2 = 32x2x4, 3 = 16x8x2 (x, y, z).  Results are the

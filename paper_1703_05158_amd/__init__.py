@@ -96,6 +96,7 @@ _sig = {
     "lbm_get_zieb": (ct.c_int, [_H, _dp]),
     "lbm_set_body_force": (ct.c_int, [_H, ct.c_void_p]),
     "lbm_drag_gradient": (ct.c_int, [_H, ct.c_int32, ct.c_int32, _dp, ct.c_void_p, ct.c_void_p]),
+    "lbm_release_memory": (ct.c_int, [_H]),
     "lbm_set_tile": (ct.c_int, [_H, ct.c_int32]),
     "lbm_get_tile": (ct.c_int, [_H, ct.POINTER(ct.c_int32)]),
     "lbm_autotune_tile": (ct.c_int, [_H, ct.c_int32, ct.c_char_p, ct.POINTER(ct.c_int32), _dp]),
@@ -339,6 +340,11 @@ def lbm_drag_gradient(h, nsteps, ckpt, n_bodies):
     return J.value, dF, dV[:n_bodies]
 
 
+def lbm_release_memory(h) -> None:
+    """Free the device memory kept from the handle's last drag gradient."""
+    _check(h, _L.lbm_release_memory(h))
+
+
 TILE_SHAPES = ("64x2x2", "32x4x2", "32x2x4", "16x8x2")
 
 
@@ -525,6 +531,9 @@ class Lattice:
 
     def drag_gradient(self, nsteps, ckpt):
         return lbm_drag_gradient(self.h, nsteps, ckpt, self.info()["n_bodies"])
+
+    def release_memory(self):
+        lbm_release_memory(self.h)
 
     def set_tile(self, shape):
         lbm_set_tile(self.h, shape)

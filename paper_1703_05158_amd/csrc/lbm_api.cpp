@@ -1628,6 +1628,15 @@ lbm_status lbm_drag_gradient(lbm_handle h, int32_t nsteps, int32_t ckpt, double 
     return LBM_OK;
 }
 
+lbm_status lbm_release_memory(lbm_handle h)
+{
+    if (!h) return LBM_ERR_ARG;
+    std::lock_guard<std::mutex> lock(kept_mutex);
+    kept_remove(h);
+    give_back(h);
+    return LBM_OK;
+}
+
 lbm_status lbm_set_tile(lbm_handle h, int32_t shape)
 {
     if (!h) return LBM_ERR_ARG;

@@ -191,3 +191,7 @@ def test_device_memory_comes_from_one_place(P):
     body = txt[txt.index("hipError_t device_alloc("):]
     body = body[:body.index("\n}\n")]
     assert calls == ["lbm_api.cpp"] * len(re.findall(r"\bhipMalloc\s*\(", body))
+
+
+def test_release_memory_null_handle(P):
+    assert ct.CDLL(P.LIB_PATH).lbm_release_memory(None) == 1

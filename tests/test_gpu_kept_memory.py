@@ -60,3 +60,18 @@ def test_given_back_when_an_allocation_would_fail(torch_stream):
         J2, gF2, gV2 = lat.drag_gradient(20, 1)
         assert J2 == J and (gF2 == gF).all() and (gV2 == gV).all()
         lat.close()
+
+
+def test_released_to_other_allocators(torch_stream):
+    import torch
+    lat, own, state, (J, gF, gV) = _keeps(torch_stream, _case(), 20)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    lat.release_memory()
+    lat.release_memory()  # nothing left: no error
+    assert lat.info()["device_bytes"] == own
+    assert torch.cuda.mem_get_info()[0] >= free + GIB
+    lat.set_state(state)
+    J2, gF2, gV2 = lat.drag_gradient(20, 1)
+    assert J2 == J and (gF2 == gF).all() and (gV2 == gV).all()
+    lat.close()
