@@ -9,6 +9,7 @@
 
 #include <algorithm>
 #include <array>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -20,6 +21,7 @@
 #include <new>
 #include <sstream>
 #include <string>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -857,6 +859,33 @@ static lbm_status refresh_order(lbm_ctx *h, const double *table, int32_t n)
     return LBM_OK;
 }
 
+// Wait until half k of the staging buffer is free: its last table has been
+// read.  Work queued after that table is not waited for.  A stream with nothing
+// left to do, or with an error, ends the wait too (the word does not change
+// where the table's kernel failed, or was captured and not launched); asking
+// costs a command on the stream, so it is asked every tenth of a millisecond.
+static lbm_status wait_table_read(lbm_ctx *h, int k)
+{
+    auto read = [&] { return __atomic_load_n(h->seen + k, __ATOMIC_ACQUIRE) == h->ticket[k]; };
+    for (int spin = 0; spin < 2000; ++spin)
+        if (read()) return LBM_OK;
+    auto asked = std::chrono::steady_clock::now();
+    while (!read()) {
+        std::this_thread::yield();
+        const auto now = std::chrono::steady_clock::now();
+        if (now - asked < std::chrono::microseconds(100)) continue;
+        asked = now;
+        const hipError_t e = hipStreamQuery(h->stream);
+        if (e == hipErrorNotReady) {
+            (void)hipGetLastError();
+            continue;
+        }
+        HIP_TRY(h, e);
+        return LBM_OK;
+    }
+    return LBM_OK;
+}
+
 lbm_status lbm_set_bodies(lbm_handle h, int32_t n, const double *X, const double *V, const double *Omega,
                           const double *R)
 {
@@ -876,13 +905,9 @@ lbm_status lbm_set_bodies(lbm_handle h, int32_t n, const double *X, const double
         if (!(R[b] > 0.0 && R[b] < rmax))
             return fail(h, LBM_ERR_ARG, "sphere %d radius %g outside (0, %g)", b, R[b], rmax);
     }
-    // this half of the staging buffer is free once its last table has been
-    // read; a short look at the word that says so, else the stream
     const int k = h->half;
     double *const stage = h->pinned + (size_t)k * kBodyStride * std::max(h->cfg.max_bodies, 1);
-    bool read = false;
-    for (int spin = 0; spin < 2000 && !read; ++spin) read = __atomic_load_n(h->seen + k, __ATOMIC_ACQUIRE) == h->ticket[k];
-    if (!read) HIP_TRY(h, hipStreamSynchronize(h->stream));
+    TRY(wait_table_read(h, k));
     for (int b = 0; b < n; ++b) {
         double *t = stage + (size_t)b * kBodyStride;
         for (int a = 0; a < 3; ++a) {
