@@ -1880,7 +1880,11 @@ lbm_status batch_build(lbm_batch_ctx *b)
     BHIP_TRY(b, hipMemcpyAsync(b->d_members, hm.data(), sizeof(BatchMember) * (size_t)n, hipMemcpyHostToDevice,
                                b->stream));
     BHIP_TRY(b, hipStreamSynchronize(b->stream));
-    b->bs = BatchStepArgs{b->d_members, b->d_cur, b->d_queue, n, tiles, forces};
+    // opposite tile orders as for one lattice, but from 7/8 of the cache on: one
+    // order / both, us per step, 64^3 boxes FP32 2 (76 MiB) 28.0 / 29.1, 5 (191 MiB)
+    // 45.6 / 46.1, 6 (229 MiB) 55.6 / 54.1, 7 (267 MiB) 64.9 / 65.0; FP16 10 (191 MiB)
+    // 66.3 / 67.2, 12 (229 MiB) 82.7 / 81.4; four 32^3 (20 MiB) 13.8 / 14.6
+    b->bs = BatchStepArgs{b->d_members, b->d_cur, b->d_queue, n, tiles, forces, backward(bytes + bytes / 7, 1)};
     int dev = 0, cus = 0;
     BHIP_TRY(b, hipGetDevice(&dev));
     BHIP_TRY(b, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));

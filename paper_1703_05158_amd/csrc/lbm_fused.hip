@@ -638,7 +638,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6, 6))) 
     for (int k = 0;; ++k) {
         int gt = xcd_item<kTileChunk<S>>(xcd, __builtin_amdgcn_readfirstlane(next[k & 1]));
         if (gt >= b.total_tiles) break;  // the XCD's later items lie beyond too
-        if (b.cur[0]) gt = b.total_tiles - 1 - gt;  // every other step, as for one lattice
+        if (b.backward && b.cur[0]) gt = b.total_tiles - 1 - gt;
         // the next tile is taken now, its atomic in flight during this one
         int pre = 0;
         if (threadIdx.x == 0) pre = atomicAdd(q, 1);

@@ -167,6 +167,7 @@ struct BatchStepArgs {
     int n;
     int total_tiles;
     int total_forces;
+    int backward;                 // every other step takes the tiles from the last to the first
 };
 
 // Reverse-mode step for the gradient of the summed sphere drag (FP32
