@@ -573,9 +573,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) 
     __shared__ FusedLds lds;
     // the previous step's forces, if nobody has read them yet (their sums
     // are in the other buffer)
+    // (a stride of 2^31 threads, a lattice of 2^23 tiles, would turn an int
+    // negative and never end)
     if (f.fin.fsum)
-        for (int i = blockIdx.x * kBlock + threadIdx.x; i < 6 * (f.fin.nb + f.fin.n_walls); i += gridDim.x * kBlock)
-            finish_value(f.fin, i);
+        for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < 6 * (size_t)(f.fin.nb + f.fin.n_walls);
+             i += (size_t)gridDim.x * kBlock)
+            finish_value(f.fin, (int)i);
     // (f is the kernel's only argument: it lies at the segment's start)
     const ArgPtr p = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
     const int t = xcd_remap<kTileChunk<S>>(blockIdx.x, gridDim.x);
