@@ -221,21 +221,24 @@ __global__ __launch_bounds__(kBlock) void k_mark_all(int *lost, int n)
 
 // The solid bitmap from the owner map: one thread per bit, two words per
 // wavefront from a ballot.  The bits of a row past its second periodic copy
-// are 0.
+// are 0.  (In rounds of the grid: a lattice one node wide has 32 bits per node,
+// and a launch less than 2^32 threads.)
 __global__ __launch_bounds__(kBlock) void k_solid_bits(GeomArgs g)
 {
     const int rw = bit_row_words(g.nx);
     const size_t words = (size_t)rw * ((size_t)g.ny * (size_t)g.nz);
-    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    const size_t w = i >> 5, r = w / (size_t)rw;
-    const int p = (int)(w - r * (size_t)rw) * 32 + (int)(i & 31);
-    bool solid = false;
-    if (w < words && p <= g.nx + 1) {
-        const int x = p == 0 ? g.nx - 1 : (p == g.nx + 1 ? 0 : p - 1);
-        solid = g.own[(size_t)x + (size_t)g.nx * r] < kVacated;
+    for (size_t first = (size_t)blockIdx.x * kBlock; first < 32 * words; first += (size_t)gridDim.x * kBlock) {
+        const size_t i = first + threadIdx.x;
+        const size_t w = i >> 5, r = w / (size_t)rw;
+        const int p = (int)(w - r * (size_t)rw) * 32 + (int)(i & 31);
+        bool solid = false;
+        if (w < words && p <= g.nx + 1) {
+            const int x = p == 0 ? g.nx - 1 : (p == g.nx + 1 ? 0 : p - 1);
+            solid = g.own[(size_t)x + (size_t)g.nx * r] < kVacated;
+        }
+        const unsigned long long m = __ballot(solid);
+        if ((threadIdx.x & 31) == 0 && w < words) g.bits[w] = (uint32_t)(m >> (threadIdx.x & 32));
     }
-    const unsigned long long m = __ballot(solid);
-    if ((threadIdx.x & 31) == 0 && w < words) g.bits[w] = (uint32_t)(m >> (threadIdx.x & 32));
 }
 
 // Lattice coordinates of node index n (a rare path: integer divisions).
@@ -680,7 +683,8 @@ hipError_t launch_mark_all(int *lost, int n, hipStream_t s)
 hipError_t launch_solid_bits(const GeomArgs &g, hipStream_t s)
 {
     const size_t bits = 32 * (size_t)bit_row_words(g.nx) * ((size_t)g.ny * (size_t)g.nz);
-    hipLaunchKernelGGL(k_solid_bits, dim3((unsigned)((bits + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, g);
+    const size_t blocks = std::min((bits + kBlock - 1) / kBlock, (size_t)1 << 22);
+    hipLaunchKernelGGL(k_solid_bits, dim3((unsigned)blocks), dim3(kBlock), 0, s, g);
     return hipGetLastError();
 }
 
