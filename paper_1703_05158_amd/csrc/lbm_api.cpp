@@ -383,7 +383,6 @@ FusedArgs fused_args(const lbm_ctx *h)
     FusedArgs f{};
     f.s = step_args(h);
     f.n_walls = h->n_walls;
-    f.nb = h->nb_state;
     f.halfway = h->cfg.bb_mode == LBM_BB_HALFWAY;
     f.fsum = h->fsum[h->fcur];
     f.wall_base = h->cfg.max_bodies;

@@ -132,7 +132,7 @@ struct FinishArgs {
 // collision and store of the step kernel.
 struct FusedArgs {
     StepArgs s;                   // the step (its wall-total fields unused)
-    int n_walls, nb, halfway;
+    int n_walls, halfway;
     unsigned long long *fsum;     // fixed-point sums: [max_bodies][6], then [n_walls][kWallRep][6]
     int wall_base;                // max_bodies: first wall copy of fsum
     const void *lrec;             // LinkRec of every solid, by owner code
@@ -256,10 +256,13 @@ hipError_t launch_walls_init(const uint8_t *wall, uint16_t *own, int N, hipStrea
 // Link records of the walls (wrec: [n_walls][kBodyStride]) and of the spheres
 // of the current geometry (bodies, nb of g).
 hipError_t launch_link_records(const GeomArgs &g, const double *wrec, hipStream_t s);
-// The whole solid bitmap from the owner map (nx, ny, nz, own, bits of g).
+// A table of n doubles from pinned host memory; `seen` (pinned) becomes `ticket`
+// when it has been read (left: device counter, 0 between launches).
 hipError_t launch_take_table(const double *from, double *to, int n, unsigned *left, unsigned *seen, unsigned ticket,
                              hipStream_t s);
+// All n marks set.
 hipError_t launch_mark_all(int *lost, int n, hipStream_t s);
+// The whole solid bitmap from the owner map (nx, ny, nz, own, bits of g).
 hipError_t launch_solid_bits(const GeomArgs &g, hipStream_t s);
 hipError_t launch_geometry(int storage, const GeomArgs &g, hipStream_t s);
 hipError_t launch_init_pop(int storage, const GeomArgs &g, const double *rho, const double *u,
