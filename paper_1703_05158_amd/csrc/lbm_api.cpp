@@ -255,11 +255,12 @@ void set_tile_shape(lbm_ctx *h, int shape)
 // 128-byte line where nx is no multiple of 32, so they have to save more there
 // than 16-bit ones.  A lattice of few tiles takes 64x2x2 in any case: its step is
 // one workgroup's chain, which is shorter where it holds fewer nodes.  Kernel
-// times 64x2x2 / 32x2x4: 24x20x28 7.0 / 7.2 us, 32^3 7.4 / 8.4, 96^3 31 / 27,
-// 72x128x128 47 / 37, 92x91x150 40 / 37, 84^3 25 / 23, 150x100x100 42 / 44 (FP16
-// 43 / 40), 130x128x100 66 / 76 (51 / 47), 161x96x96 40 / 47 (41 / 43),
-// 96x96x256 duct 81 / 66, 160x128x128 FP16 70 / 63; 32x4x2 is nowhere ahead of
-// 32x2x4 by more than 1%.
+// times 64x2x2 / 32x2x4, fixed spheres: 24x20x28 6.5 / 6.5 us, 32^3 6.7 / 6.9, 96^3
+// 28.7 / 28.7, 72x128x128 43.8 / 37.0, 92x91x150 39.6 / 39.7, 84^3 23.7 / 22.4,
+// 150x100x100 45.1 / 47.0 (FP16 41.5 / 37.1), 130x128x100 53.2 / 60.3 (48.6 / 43.9),
+// 161x96x96 44.2 / 50.0 (39.1 / 39.9), 96x96x256 59.3 / 58.3, 96x64x64 FP16 19.7 /
+// 15.9, 160x128x128 FP16 63.2 / 55.3; 32x4x2 is nowhere ahead of 32x2x4 by more than
+// 2%.
 int default_tile(const lbm_ctx *h)
 {
     const lbm_config &c = h->cfg;
@@ -278,18 +279,18 @@ int default_tile(const lbm_ctx *h)
 // caches: there a step takes a few microseconds, and dirty lines that are
 // written back only when the kernel ends are waited for.  Between, plain stores
 // leave the next state in the Infinity Cache.  Measured, hint / plain:
-// 128x128x512 duct FP32 (1276 MB, 30 steps) 8.35 / 8.70 ms, 96x96x256 duct (359
-// MB, 30) 3.41 / 3.55 ms; 160x128x128 box FP16 (200 MB, 50) 3.82 / 3.22 ms,
-// 96^3 box (134 MB, 20) 0.68 / 0.58 ms, 96x48x96 (67 MB, 20) 382 / 339 us, FP16
-// (34 MB) 337 / 331 us; 96x64x64 FP16 (30 MB, 20) 369 / 378 us, 96x40x40 (23
-// MB) 288 / 306 us, 32x32x113 (18 MB) 125 / 137 us.
+// 128x128x512 duct FP32 (1276 MB, 30 steps) 8.26 / 8.58 ms, 96x96x256 duct (359
+// MB, 30) 3.11 / 3.26 ms; 160x128x128 box FP16 (200 MB, 20) 1.40 / 1.13 ms,
+// 96^3 box (134 MB, 20) 674 / 590 us, 96x48x96 (67 MB, 20) 367 / 324 us, FP16
+// (34 MB) 328 / 307 us; 96x64x64 FP16 (30 MB, 20) 336 / 355 us, 96x40x40 (23
+// MB) 241 / 257 us, 32x32x113 (18 MB) 122 / 128 us.
 //
 // Beyond the Infinity Cache consecutive steps take the tiles in opposite
 // orders, so that a step starts on what the last one left in it (1% on the
 // 128x128x512 duct).  A state that fits has no need of it, and in one order an
 // XCD finds what it wrote itself in its own L2: one order / both, 20 steps,
-// 32x32x113 137 / 175 us, 96x40x40 306 / 326 us, 96x64x64 FP16 378 / 413 us, 96^3
-// 581 / 583 us.
+// 32x32x113 122 / 158 us, 96x40x40 241 / 256 us, 96x48x96 324 / 338 us, 96x64x64
+// FP16 335 / 338 us, 96^3 590 / 587 us.
 constexpr size_t kL2Bytes = (size_t)32 << 20, kCacheBytes = (size_t)256 << 20;
 int stream_out(size_t bytes) { return bytes <= kL2Bytes || bytes > kCacheBytes; }
 int backward(size_t bytes, int odd) { return bytes > kCacheBytes ? odd : 0; }

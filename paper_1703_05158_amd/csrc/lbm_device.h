@@ -135,8 +135,8 @@ __device__ __forceinline__ int xcd_remap(int b, int nblocks)
 }
 
 // Tiles of a step kernel with storage S in a run: as many bytes for both
-// sizes.  128x128x512 duct, 30 steps: FP32 8.34 ms with 32, 8.45 with 64, 8.69
-// with 128; FP16 7.30 ms with 32, 7.12 with 64, 7.26 with 128.
+// sizes.  128x128x512 duct, 30 steps: FP32 8.26 ms with 32, 8.35 with 64, 8.46
+// with 128; FP16 6.98 ms with 32, 6.88 with 64, 7.00 with 128.
 template <int S>
 constexpr int kTileChunk = S == 0 ? 32 : 64;
 

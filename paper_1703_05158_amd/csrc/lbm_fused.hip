@@ -29,8 +29,8 @@
 // storage instruction issue.  A wavefront issues vector and scalar
 // instructions on separate ports at the same rate (one per SIMD in four
 // cycles), so both counts matter.  On the 128x128x512 duct with 4000 spheres,
-// tile 64x2x2, per wavefront: 662 vector and 599 scalar instructions
-// (FP16), 209 us per launch; with owner codes loaded per pull source and a scan over
+// tile 64x2x2, per wavefront: 658 vector and 588 scalar instructions
+// (FP16), 206 us per launch; with owner codes loaded per pull source and a scan over
 // the workgroup (897 vector, 410 scalar, 18 loads more) it took 244 us, FP32
 // 255 against 287 us.  Masks kept per direction for the pulls as well (1305
 // scalar instructions) took 316 us: the pulls therefore go to every fluid
