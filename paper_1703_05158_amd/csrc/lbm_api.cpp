@@ -37,8 +37,8 @@ struct lbm_ctx {
     int cur = 0;                       // pop[cur] holds the current (post-collision) state
     uint16_t *own = nullptr;
     uint32_t *bits = nullptr;          // solid bitmap of own (bit_row_words)
-    int *lost = nullptr;               // 2 * max_bodies: marks of the geometry (GeomArgs), half ts those of tab[ts]
     void *lrec = nullptr;              // (max_walls + max_bodies) * kLinkRecBytes: link records by owner code
+    int *lost = nullptr;               // behind them, 2 * max_bodies: marks of the geometry, half ts those of tab[ts]
     uint8_t *wall_map = nullptr;
     double *tab[2] = {nullptr, nullptr};
     int ts = 0;                        // tab[ts]: bodies of the current state's geometry
@@ -79,14 +79,14 @@ struct lbm_ctx {
     int *flag_host = nullptr;
     double *scratch = nullptr;         // 4N doubles, export/import staging (lazy)
     // set_bodies staging, two halves of max_bodies * 10 doubles in turn, which a
-    // kernel reads in place; seen[k] (pinned too) becomes ticket[k] when half k
+    // kernel reads in place; seen[k] (behind them) becomes ticket[k] when half k
     // has been read
     double *pinned = nullptr;
     unsigned *seen = nullptr;
     unsigned ticket[2] = {0, 0};
     int half = 0;                      // the half of the next table
     int n_staged = 0;                  // spheres of the last table, which lies in the other half
-    unsigned *left = nullptr;          // device counter of k_take_table
+    unsigned *left = nullptr;          // device counter of k_take_table, behind flag
     double *forces_pin = nullptr;      // (max_bodies + max_walls) * 6 doubles, get_forces staging
     int *order = nullptr;              // max_bodies: sphere order of the link pass (Morton order of the centres)
     int *order_pin = nullptr;          // its host staging
@@ -479,18 +479,16 @@ lbm_status update_geometry(lbm_ctx *h, GeomArgs &g, int to)
     return LBM_OK;
 }
 
-// Rebuild the whole owner map: walls, then the spheres of tab[ts].
+// Rebuild the whole owner map and the solid bitmap: walls, then the spheres of
+// tab[ts], whose link records are written too.
 lbm_status rasterize_full(lbm_ctx *h)
 {
     GeomArgs g = geom(h);
-    HIP_TRY(h, launch_link_records(g, h->wrec, h->stream));
     g.bodies2 = g.bodies;  // stamp only
     g.nb2 = g.nb;
     g.nb = 0;
-    HIP_TRY(h, launch_walls_init(h->wall_map, h->own, h->N, h->stream));
-    TRY(update_geometry(h, g, h->ts));
-    HIP_TRY(h, launch_solid_bits(g, h->stream));
-    return LBM_OK;
+    HIP_TRY(h, launch_walls_init(g, h->wall_map, h->stream));
+    return update_geometry(h, g, h->ts);
 }
 
 // Move from the geometry of tab[ts] to that of tab[1-ts] (bodies set since
@@ -710,13 +708,13 @@ lbm_status lbm_create(const lbm_config *cfg, lbm_handle *out)
     };
     const size_t popb = (size_t)kQ * h->Ns * h->sbytes;
     const int nbt = c.max_bodies + c.max_walls;
+    const size_t lrecb = (size_t)kLinkRecBytes * std::max(nbt, 1), lostb = sizeof(int) * 2 * (size_t)std::max(c.max_bodies, 1);
     set_tile_shape(h, default_tile(h));
     if (dalloc(h, &h->pop[0], popb) != hipSuccess || dalloc(h, &h->pop[1], popb) != hipSuccess ||
         dalloc(h, &h->own, sizeof(uint16_t) * N + 4) != hipSuccess ||
         dalloc(h, &h->bits, sizeof(uint32_t) * (bit_row_words(c.nx) * ((size_t)c.ny * (size_t)c.nz) + kBitPad)) !=
             hipSuccess ||
-        dalloc(h, &h->lost, sizeof(int) * 2 * (size_t)std::max(c.max_bodies, 1)) != hipSuccess ||
-        dalloc(h, &h->lrec, (size_t)kLinkRecBytes * std::max(nbt, 1)) != hipSuccess ||
+        dalloc(h, &h->lrec, lrecb + lostb) != hipSuccess ||
         dalloc(h, &h->wall_map, (size_t)N) != hipSuccess ||
         dalloc(h, &h->tab[0], sizeof(double) * kBodyStride * std::max(c.max_bodies, 1)) != hipSuccess ||
         dalloc(h, &h->tab[1], sizeof(double) * kBodyStride * std::max(c.max_bodies, 1)) != hipSuccess ||
@@ -728,19 +726,21 @@ lbm_status lbm_create(const lbm_config *cfg, lbm_handle *out)
         dalloc(h, &h->order, sizeof(int) * std::max(c.max_bodies, 1)) != hipSuccess ||
         dalloc(h, &h->zstate, sizeof(ZiebState)) != hipSuccess ||
         dalloc(h, &h->zpart, sizeof(double) * (3 * kZiebMaxBlocks + 1)) != hipSuccess ||
-        dalloc(h, &h->left, sizeof(unsigned)) != hipSuccess || dalloc(h, &h->flag, sizeof(int)) != hipSuccess)
+        dalloc(h, &h->flag, 2 * sizeof(int)) != hipSuccess)
         return bail(LBM_ERR_OOM);
-    if (cleared(hipHostMalloc((void **)&h->pinned, 2 * sizeof(double) * kBodyStride * std::max(c.max_bodies, 1))) !=
-            hipSuccess ||
-        cleared(hipHostMalloc((void **)&h->seen, 2 * sizeof(unsigned))) != hipSuccess ||
+    h->lost = reinterpret_cast<int *>(static_cast<char *>(h->lrec) + lrecb);
+    h->left = reinterpret_cast<unsigned *>(h->flag + 1);
+    const size_t stageb = 2 * sizeof(double) * kBodyStride * (size_t)std::max(c.max_bodies, 1);
+    if (cleared(hipHostMalloc((void **)&h->pinned, stageb + 2 * sizeof(unsigned))) != hipSuccess ||
         cleared(hipHostMalloc((void **)&h->forces_pin, sizeof(double) * 6 * std::max(nbt, 1))) != hipSuccess ||
         cleared(hipHostMalloc((void **)&h->order_pin, sizeof(int) * std::max(c.max_bodies, 1))) != hipSuccess ||
         cleared(hipHostMalloc((void **)&h->flag_host, sizeof(int))) != hipSuccess)
         return bail(LBM_ERR_OOM);
+    h->seen = reinterpret_cast<unsigned *>(reinterpret_cast<char *>(h->pinned) + stageb);
     h->seen[0] = h->seen[1] = 0;
     if (hipEventCreateWithFlags(&h->stage_evt, hipEventDisableTiming) != hipSuccess) return bail(LBM_ERR_HIP);
     if (hipMemsetAsync(h->wall_map, 0, (size_t)N, h->stream) != hipSuccess ||
-        hipMemsetAsync(h->lost, 0, sizeof(int) * 2 * (size_t)std::max(c.max_bodies, 1), h->stream) != hipSuccess ||
+        hipMemsetAsync(h->lost, 0, lostb, h->stream) != hipSuccess ||
         hipMemsetAsync(h->pop[0], 0, popb, h->stream) != hipSuccess ||
         hipMemsetAsync(h->pop[1], 0, popb, h->stream) != hipSuccess ||
         hipMemsetAsync(h->acc, 0, sizeof(double) * 6 * std::max(nbt, 1), h->stream) != hipSuccess ||
@@ -748,8 +748,7 @@ lbm_status lbm_create(const lbm_config *cfg, lbm_handle *out)
             hipSuccess ||
         hipMemsetAsync(h->fsum[1], 0, sizeof(unsigned long long) * std::max(fsum_entries(c), (size_t)1), h->stream) !=
             hipSuccess ||
-        hipMemsetAsync(h->flag, 0, sizeof(int), h->stream) != hipSuccess ||
-        hipMemsetAsync(h->left, 0, sizeof(unsigned), h->stream) != hipSuccess ||
+        hipMemsetAsync(h->flag, 0, 2 * sizeof(int), h->stream) != hipSuccess ||
         hipMemsetAsync(h->zpart + 3 * kZiebMaxBlocks, 0, sizeof(double), h->stream) != hipSuccess)
         return bail(LBM_ERR_HIP);
     if (rasterize_full(h) != LBM_OK) return bail(LBM_ERR_HIP);
@@ -769,12 +768,11 @@ void lbm_destroy(lbm_handle h)
     give_back(h);
     for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
     free_wall_links(h);
-    void *dev[] = {h->pop[0], h->pop[1], h->own, h->bits, h->lost, h->lrec, h->wall_map, h->tab[0], h->tab[1], h->walls, h->wrec,
-                   h->acc, h->fsum[0], h->fsum[1], h->order, h->left, h->flag, h->scratch, h->zstate, h->zpart};
+    void *dev[] = {h->pop[0], h->pop[1], h->own, h->bits, h->lrec, h->wall_map, h->tab[0], h->tab[1], h->walls, h->wrec,
+                   h->acc, h->fsum[0], h->fsum[1], h->order, h->flag, h->scratch, h->zstate, h->zpart};
     for (void *p : dev)
         if (p) (void)hipFree(p);
     if (h->pinned) (void)hipHostFree(h->pinned);
-    if (h->seen) (void)hipHostFree(h->seen);
     if (h->forces_pin) (void)hipHostFree(h->forces_pin);
     if (h->order_pin) (void)hipHostFree(h->order_pin);
     if (h->flag_host) (void)hipHostFree(h->flag_host);
@@ -817,6 +815,7 @@ lbm_status lbm_set_walls(lbm_handle h, const uint8_t *wall_id, int32_t n_walls, 
     h->wall_host.assign(wall_id, wall_id + h->N);
     TRY(build_wall_links(h, wall_id, n_walls));
     h->n_walls = n_walls;
+    HIP_TRY(h, launch_link_records(geom(h), h->wrec, h->stream));
     return rasterize_full(h);
 }
 

@@ -180,12 +180,6 @@ __device__ __forceinline__ void column_range(const double *B, const Box &bx, con
     while (hi >= lo && !inside(B, px, py, wrap1(hi, nz), nx, ny, nz)) --hi;
 }
 
-__global__ __launch_bounds__(kBlock) void k_walls_init(const uint8_t *wall, uint16_t *own, int N)
-{
-    const int n = blockIdx.x * kBlock + threadIdx.x;
-    if (n < N) own[n] = wall[n] ? (uint16_t)(wall[n] - 1) : kFluid;
-}
-
 __global__ __launch_bounds__(kBlock) void k_link_records(GeomArgs g, const double *wrec)
 {
     const int i = blockIdx.x * kBlock + threadIdx.x;
@@ -219,11 +213,13 @@ __global__ __launch_bounds__(kBlock) void k_mark_all(int *lost, int n)
     if (i < n) lost[i] = 1;
 }
 
-// The solid bitmap from the owner map: one thread per bit, two words per
-// wavefront from a ballot.  The bits of a row past its second periodic copy
-// are 0.  (In rounds of the grid: a lattice one node wide has 32 bits per node,
-// and a launch less than 2^32 threads.)
-__global__ __launch_bounds__(kBlock) void k_solid_bits(GeomArgs g)
+// The solid bitmap from the owner map, or (kWalls) that map and the bitmap of a
+// lattice that holds only walls: one thread per bit, two words per wavefront
+// from a ballot.  The bits of a row past its second periodic copy are 0.  (In
+// rounds of the grid: a lattice one node wide has 32 bits per node, and a launch
+// less than 2^32 threads.)
+template <bool kWalls>
+__global__ __launch_bounds__(kBlock) void k_solid_bits(GeomArgs g, const uint8_t *wall)
 {
     const int rw = bit_row_words(g.nx);
     const size_t words = (size_t)rw * ((size_t)g.ny * (size_t)g.nz);
@@ -234,7 +230,14 @@ __global__ __launch_bounds__(kBlock) void k_solid_bits(GeomArgs g)
         bool solid = false;
         if (w < words && p <= g.nx + 1) {
             const int x = p == 0 ? g.nx - 1 : (p == g.nx + 1 ? 0 : p - 1);
-            solid = g.own[(size_t)x + (size_t)g.nx * r] < kVacated;
+            const size_t n = (size_t)x + (size_t)g.nx * r;
+            if constexpr (kWalls) {
+                const uint8_t v = wall[n];
+                solid = v != 0;
+                if (p == x + 1) g.own[n] = solid ? (uint16_t)(v - 1) : kFluid;
+            } else {
+                solid = g.own[n] < kVacated;
+            }
         }
         const unsigned long long m = __ballot(solid);
         if ((threadIdx.x & 31) == 0 && w < words) g.bits[w] = (uint32_t)(m >> (threadIdx.x & 32));
@@ -651,12 +654,6 @@ template <int S> struct MacroK { static constexpr auto fn = k_export_macro<S>; }
 
 }  // namespace
 
-hipError_t launch_walls_init(const uint8_t *wall, uint16_t *own, int N, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_walls_init, dim3(nblk(N)), dim3(kBlock), 0, s, wall, own, N);
-    return hipGetLastError();
-}
-
 hipError_t launch_link_records(const GeomArgs &g, const double *wrec, hipStream_t s)
 {
     const int n = g.n_walls + g.nb;
@@ -680,11 +677,21 @@ hipError_t launch_mark_all(int *lost, int n, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_solid_bits(const GeomArgs &g, hipStream_t s)
+static dim3 bits_grid(const GeomArgs &g)
 {
     const size_t bits = 32 * (size_t)bit_row_words(g.nx) * ((size_t)g.ny * (size_t)g.nz);
-    const size_t blocks = std::min((bits + kBlock - 1) / kBlock, (size_t)1 << 22);
-    hipLaunchKernelGGL(k_solid_bits, dim3((unsigned)blocks), dim3(kBlock), 0, s, g);
+    return dim3((unsigned)std::min((bits + kBlock - 1) / kBlock, (size_t)1 << 22));
+}
+
+hipError_t launch_walls_init(const GeomArgs &g, const uint8_t *wall, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_solid_bits<true>, bits_grid(g), dim3(kBlock), 0, s, g, wall);
+    return hipGetLastError();
+}
+
+hipError_t launch_solid_bits(const GeomArgs &g, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_solid_bits<false>, bits_grid(g), dim3(kBlock), 0, s, g, (const uint8_t *)nullptr);
     return hipGetLastError();
 }
 

@@ -252,7 +252,8 @@ hipError_t launch_adj_reduce(const double *dF_tile, int n_tiles, double *dF, hip
 // at first[b], n in all.
 hipError_t launch_adj_dv(const double *dW, const int *first, int n, int nb, double *dV, hipStream_t s);
 
-hipError_t launch_walls_init(const uint8_t *wall, uint16_t *own, int N, hipStream_t s);
+// The owner map and the solid bitmap of the walls alone (wall: voxel map).
+hipError_t launch_walls_init(const GeomArgs &g, const uint8_t *wall, hipStream_t s);
 // Link records of the walls (wrec: [n_walls][kBodyStride]) and of the spheres
 // of the current geometry (bodies, nb of g).
 hipError_t launch_link_records(const GeomArgs &g, const double *wrec, hipStream_t s);
